@@ -1,10 +1,11 @@
 // Batched rendering of many cameras over uneven bricks.
 //
 // One persistent launch walks a queue of (camera, brick, screen tile) items.
-// Each wave pops an item with one atomic, takes its rays as a pool, and marches
-// them a few segments at a time; lanes whose ray has finished (left the brick or
-// terminated early) write their fragment and are refilled from the pool with
-// ballot/popcount compaction, so a wave is not held back by its longest ray.  A
+// Each wave pops a chunk of an item with one atomic, takes its rays as a pool, and
+// marches them a few segments at a time, four lanes per ray; lanes whose ray has
+// finished (left the brick or terminated early) write its fragment and are refilled
+// from the pool with ballot/popcount compaction, so a wave is not held back by its
+// longest ray.  A
 // wave keeps one (camera, brick) at a time so brick and camera descriptors stay
 // wave-uniform.  A tile compositor then merges, per camera tile, the fragments of
 // every item covering it.  Reset + march + composite are captured once into a
@@ -39,35 +40,48 @@ struct BatchG {
   int* slot_count;
 };
 
-// Segments between refill checks.  A return to the refill point costs a ballot,
-// the pool bookkeeping and a fresh exact macrocell-run computation, so checks are
-// kept rare; a lane that finishes early waits at most this many segments.
-constexpr int kChunk = 128;
+// A march returns for a refill once fewer lanes than this are marching
 constexpr int kRefillLanes = 32;
 
-__global__ void reset_head_kernel(int* head) { *head = 0; }
+__global__ void reset_head_kernel(int* head, int first) { *head = first; }
 __global__ void zero_counts_kernel(int* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
+// A wave marches the queue's rays with the four lanes of a quad per ray (march.h), 16 at a
+// time: 4 x 4 pixel patches of a tile where the tile's shape allows.  What bounds it: the
+// chain of a launch's longest ray where a frame has few rays (one 256^3 brick at 1024^2:
+// 0.56 ms with one lane per ray, 0.14 ms with four), the texture path on bricks much larger
+// than the L2 (the 8 GB brick at 3840 x 2160: 12.5 -> 6.2 ms, a wave's loads meeting less than
+// half as many cache lines), VALU issue (94% busy) on the multi-camera batch of 27 FP16
+// bricks: 11.1 ms with one lane, 11.4 ms with four, which run everything.
 template <typename T, bool SKIP, bool WIDE, bool ISO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void batch_march_kernel(SceneG sc, BatchG bg, const float4* __restrict__ tf) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void batch_march_kernel(
+    SceneG sc, BatchG bg, const float4* __restrict__ tf) {
   extern __shared__ float4 tf_lds[];
-  float4* tfb = tf_lds;
-  float4* tfs = tf_lds + sc.ntf;
-  stage_tf(tf, sc.ntf, tfb, tfs, threadIdx.x, 256);
+  stage_tf_records(tf, sc.ntf, tf_lds, threadIdx.x, 256);
   __syncthreads();
 
-  const int lane = threadIdx.x & 63;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  constexpr int L = 4;
+  const int lane = threadIdx.x & 63, k = lane & (L - 1);
+  const uint64_t lt_mask = ~(~0ull << (lane & (64 - L)));  // the lanes of lower rays
   const int tp = bg.tile_w * bg.tile_h;
+  const bool patches = ((bg.tile_w | bg.tile_h) & 3) == 0;
+  const int patches_x = bg.tile_w >> 2;
+
+  // the queue's unit is a chunk of the rays of a wave (it divides every tile's pixels); a wave's first one is its own, so
+  // that a launch starts without thousands of atomics on one counter, and the first
+  // chunks go to different CUs
+  constexpr int kChunkRays = 64 / L;
+  const int per_item = tp / kChunkRays, n_chunks = bg.n_items * per_item;
+  int first = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
 
   int cur_cam = -1, cur_brick = -1;
   int pool_item = -1, pool_next = 0, pool_left = 0;
-  int pending = -1;
+  int pending = -1;  // a chunk
   bool exhausted = false;
   bool active = false;
-  RayState r;
+  LaneRay r;
   size_t slot = 0;
 
   while (true) {
@@ -77,49 +91,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void b
       if (idle == 0) break;
       if (pool_left == 0) {
         if (pending >= 0 || exhausted) break;
-        int it = 0;
-        if (lane == 0) it = atomicAdd(bg.head, 1);
+        int c = first;
+        if (c < 0) {
+          if (lane == 0) c = atomicAdd(bg.head, 1);
+        }
+        first = -1;
         // wave-uniform: the item, and so the brick, live in scalar registers
-        it = __builtin_amdgcn_readfirstlane(__shfl(it, 0));
-        if (it >= bg.n_items) {
+        c = __builtin_amdgcn_readfirstlane(c);
+        if (c >= n_chunks) {
           exhausted = true;
           break;
         }
-        if (bg.item_count && lane == 0) atomicAdd(bg.item_count + it, 1);
-        const BatchItem I = bg.items[it];
+        const int it = c / per_item;
+        if (bg.item_count && lane == 0 && c % per_item == 0) atomicAdd(bg.item_count + it, 1);
+        const BatchItem I = ld_uniform(bg.items, it);
         if (I.cam != cur_cam || I.brick != cur_brick) {
           if (__ballot(active) != 0) {  // drain the current rays first
-            pending = it;
+            pending = c;
             break;
           }
           cur_cam = I.cam;
           cur_brick = I.brick;
         }
         pool_item = it;
-        pool_next = 0;
-        pool_left = tp;
+        pool_next = (c % per_item) * kChunkRays;
+        pool_left = kChunkRays;
       }
-      const int n_idle = __popcll(idle);
+      const int n_idle = __popcll(idle) / L;
       const int take = min(n_idle, pool_left);
-      const int rank = __popcll(idle & lt_mask);
+      const int rank = __popcll(idle & lt_mask) / L;
       if (!active && rank < take) {
-        const int pix = pool_next + rank;
-        const BatchItem I = bg.items[pool_item];
-        const CamG& cam = bg.cams[cur_cam];
-        const int px = I.tx * bg.tile_w + pix % bg.tile_w;
-        const int py = I.ty * bg.tile_h + pix / bg.tile_w;
-        slot = (size_t)pool_item * tp + pix;
+        const int i = pool_next + rank;
+        const BatchItem I = ld_uniform(bg.items, pool_item);
+        const CamG cam = ld_uniform(bg.cams, cur_cam);
+        int ux, uy;  // pixel inside the tile
+        if (patches) {
+          const int p = i >> 4;
+          ux = (p % patches_x) * 4 + (i & 3);
+          uy = (p / patches_x) * 4 + ((i >> 2) & 3);
+        } else {
+          ux = i % bg.tile_w;
+          uy = i / bg.tile_w;
+        }
+        const int px = I.tx * bg.tile_w + ux;
+        const int py = I.ty * bg.tile_h + uy;
+        slot = (size_t)pool_item * tp + uy * bg.tile_w + ux;
         bool hit = false;
         if (px < cam.W && py < cam.H) {
           double d[3];
           camera_ray(cam, px, py, d);
-          hit = ray_start<T, WIDE, ISO>(sc, bg.bricks[cur_brick], cam.eye, d, r);
+          hit = lane_begin<T, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, cur_brick), cam.eye, d, k, r);
         }
-        if (hit) {
+        // (a hit with no samples is an empty fragment at its depth)
+        const bool none = hit && r.m + k < 0;
+        if (hit && !none) {
           active = true;
-        } else {
+        } else if (k == 0) {
           bg.frag_rgba[slot] = make_float4(0.f, 0.f, 0.f, 0.f);
-          bg.frag_depth[slot] = INFINITY;
+          bg.frag_depth[slot] = none ? r.t_in : INFINITY;
           if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
         }
       }
@@ -129,12 +158,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void b
     // ---- nothing to march: switch to the pending item or finish
     if (__ballot(active) == 0) {
       if (pending >= 0) {
-        const BatchItem I = bg.items[pending];
+        pool_item = pending / per_item;
+        pool_next = (pending % per_item) * kChunkRays;
+        pool_left = kChunkRays;
+        const BatchItem I = ld_uniform(bg.items, pool_item);
         cur_cam = I.cam;
         cur_brick = I.brick;
-        pool_item = pending;
-        pool_next = 0;
-        pool_left = tp;
         pending = -1;
         continue;
       }
@@ -146,10 +175,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void b
       // early return for a refill (fewer than half the lanes marching), only while
       // a refill can take rays
       const int min_lanes = (!exhausted && pending < 0) ? kRefillLanes : 0;
-      if (ray_advance<T, SKIP, WIDE, ISO>(sc, bg.bricks[cur_brick], tfb, tfs, r, kChunk, min_lanes)) {
-        bg.frag_rgba[slot] = make_float4(r.cr, r.cg, r.cb, 1.f - r.T);
-        bg.frag_depth[slot] = (float)r.t_in;
-        if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
+      if (lane_advance<T, SKIP, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, cur_brick), tf_lds, r, LaneCfg<L>::kTrips,
+                                              min_lanes)) {
+        if (k == L - 1) {
+          bg.frag_rgba[slot] = make_float4(r.cr, r.cg, r.cb, 1.f - r.tr);
+          bg.frag_depth[slot] = r.t_in;
+          if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
+        }
         active = false;
       }
     }
@@ -425,9 +457,9 @@ static hipError_t enqueue_batch(dpr_world w, BatchState* b, hipStream_t st, bool
   }
   const bool f16 = w->bricks[b->brick_sel >= 0 ? b->brick_sel : 0].dtype == DPR_F16;
   size_t lds = 2 * sizeof(float4) * (size_t)sc.ntf;
-  hipLaunchKernelGGL(reset_head_kernel, dim3(1), dim3(1), 0, st, b->head);
-  if (timed) (void)hipEventRecord(b->ev[0], st);
   const int iso = sc.iso_on ? 1 : 0;
+  hipLaunchKernelGGL(reset_head_kernel, dim3(1), dim3(1), 0, st, b->head, 4 * b->grid[iso]);
+  if (timed) (void)hipEventRecord(b->ev[0], st);
   const void* fn = march_fn(f16, b->skip, b->wide(), iso);
   void* args[] = {(void*)&sc, (void*)&g, (void*)&w->tf_dev};
   const hipError_t le = hipLaunchKernel(fn, dim3(b->grid[iso]), dim3(256), args, lds, st);

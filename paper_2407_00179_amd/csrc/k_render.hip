@@ -49,9 +49,7 @@ __global__ __launch_bounds__(256) void march_kernel(SceneG sc, BrickG b, CamG ca
                                                     float4* __restrict__ out_rgba, float* __restrict__ out_depth,
                                                     int* __restrict__ out_count, int tiles_x, int n_tiles) {
   extern __shared__ float4 tf_lds[];
-  float4* tfb = tf_lds;
-  float4* tfs = tf_lds + sc.ntf;
-  stage_tf(tf, sc.ntf, tfb, tfs, threadIdx.x, 256);
+  stage_tf_records(tf, sc.ntf, tf_lds, threadIdx.x, 256);
   __syncthreads();
   const int nb = gridDim.x;
   const int per = (nb + 7) >> 3;
@@ -64,12 +62,12 @@ __global__ __launch_bounds__(256) void march_kernel(SceneG sc, BrickG b, CamG ca
   if (px >= cam.W || py >= cam.H) return;
   double d[3];
   camera_ray(cam, px, py, d);
-  RayState r;
+  LaneRay r;
   const size_t p = (size_t)py * cam.W + px;
-  if (ray_start<T, WIDE, ISO>(sc, b, cam.eye, d, r)) {
-    ray_advance<T, SKIP, WIDE, ISO>(sc, b, tfb, tfs, r, 0x7fffffff);
-    out_rgba[p] = make_float4(r.cr, r.cg, r.cb, 1.f - r.T);
-    out_depth[p] = (float)r.t_in;
+  if (lane_begin<T, WIDE, ISO, 1>(sc, b, cam.eye, d, 0, r)) {
+    lane_advance<T, SKIP, WIDE, ISO, 1>(sc, b, tf_lds, r, 0x7fffffff, 0);
+    out_rgba[p] = make_float4(r.cr, r.cg, r.cb, 1.f - r.tr);
+    out_depth[p] = r.t_in;
   } else {
     r.n = 0;
     out_rgba[p] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -108,7 +106,7 @@ __global__ __launch_bounds__(256) void gather_probe_kernel(SceneG sc, BrickG b, 
   float acc = 0.f;
   double d[3];
   camera_ray(cam, px, py, d);
-  RayState r;
+  RaySetup r;
   if (k1 > k0 && ray_begin(sc, b, cam.eye, d, r)) {
     const int64_t half = 0x80000000ll;
     int64_t last[3];

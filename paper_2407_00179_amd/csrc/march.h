@@ -1,14 +1,8 @@
 // Resumable per-ray emission-absorption march through one brick.
 //
-// Sample points advance in exact 32.32 fixed point (global voxel-centre units),
-// so the point of segment s is the same integer whichever way the ray got there:
-// in one call, in budgeted slices (persistent kernel), with or without skipping.
-// The lattice is walked in runs of consecutive segments whose sample points share
-// one macrocell; the run length is computed exactly in integers, a run in a
-// macrocell of majorant 0 is skipped in O(1), and the other runs sample every
-// segment with no per-sample macrocell logic.  Voxel gathers of the next sample
-// are issued before the current sample is shaded.  For bricks below 4 GiB a voxel
-// address is a 32-bit byte offset from the brick base.
+// Sample points advance in exact 32.32 fixed point, so the point of segment s is the
+// same integer whichever way the ray got there: by one lane or four, in one call or in
+// budgeted slices (persistent kernel), with or without skipping.
 //
 // Iso-surfaces (ISO): the sides (v >= v_iso) of consecutive samples are compared
 // at every lattice point the brick owns (those in [t_in, t_out)); the first change
@@ -24,20 +18,14 @@
 namespace dpr {
 
 constexpr double kFix = 4294967296.0;  // 2^32
-constexpr int kShadeRun = 4;            // samples per run in a non-empty macrocell (even)
 
-struct RayState {
-  int64_t p[3];          // sample point of segment s, 32.32 fixed point (global voxel-centre coords)
+// A ray clipped to a brick.
+struct RaySetup {
+  int64_t p[3];          // sample point of segment s0, 32.32 fixed point (global voxel-centre coords)
   int64_t dp[3];         // advance per segment
   double t_in, t_out;    // clipped parametric range (world units)
-  double tau;            // optical depth accumulated so far
-  int s, s0, s1;         // next segment, first and last segment
-  int n;                 // logical samples processed
+  int s0, s1;            // first and last segment
   float dl_first, dl_last;  // D * clipped length of the first / last segment
-  float T, cr, cg, cb;   // transmittance and premultiplied colour
-  float pv;              // iso-surfaces: value of the previous sample
-  int pst;               // iso-surfaces: bit 0 side of the previous sample, bit 1 the next
-                         // sample closes a tested pair, bit 2 pv holds the value
 };
 
 constexpr int kIsoSide = 1, kIsoPair = 2, kIsoKnown = 4;
@@ -45,7 +33,7 @@ constexpr int kIsoSide = 1, kIsoPair = 2, kIsoKnown = 4;
 // Clip the ray against the brick's owned box and set up its march.  Returns false
 // on a miss (zero-length chords included).
 __device__ __forceinline__ bool ray_begin(const SceneG& sc, const BrickG& b, const double o[3], const double d[3],
-                                          RayState& r) {
+                                          RaySetup& r) {
   double lo[3], hi[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -68,7 +56,7 @@ __device__ __forceinline__ bool ray_begin(const SceneG& sc, const BrickG& b, con
     ll = fmin((s1 + 1) * dt, r.t_out) - fmax(s1 * dt, r.t_in);
   }
   // (s1 < s0 only through rounding at a vanishing chord: a hit with no samples)
-  r.s = r.s0 = s0;
+  r.s0 = s0;
   r.s1 = s1;
   r.dl_first = sc.density * (float)lf;
   r.dl_last = sc.density * (float)ll;
@@ -80,32 +68,7 @@ __device__ __forceinline__ bool ray_begin(const SceneG& sc, const BrickG& b, con
     r.p[a] = __double2ll_rn(g * kFix);
     r.dp[a] = __double2ll_rn(dt * dv * kFix);
   }
-  r.tau = 0.0;
-  r.n = 0;
-  r.T = 1.f;
-  r.cr = r.cg = r.cb = 0.f;
   return true;
-}
-
-// Largest j >= 0 with p + j*dp inside [b_lo, b_hi) on one axis (the current point
-// is inside).  Exact: floating-point quotient corrected in integers.
-__device__ __forceinline__ int steps_inside(int64_t p, int64_t dp, int64_t b_lo, int64_t b_hi, int cap) {
-  int64_t num, den;
-  if (dp > 0) {
-    if (b_hi == INT64_MAX) return cap;
-    num = b_hi - 1 - p;
-    den = dp;
-  } else if (dp < 0) {
-    if (b_lo == INT64_MIN) return cap;
-    num = p - b_lo;
-    den = -dp;
-  } else {
-    return cap;
-  }
-  int64_t q = (int64_t)((double)num / (double)den);
-  if (q * den > num) --q;
-  else if ((q + 1) * den <= num) ++q;
-  return q < (int64_t)cap ? (int)q : cap;
 }
 
 // Voxel index (stored, relative to the brick) and fraction along one axis of a
@@ -142,45 +105,32 @@ struct Voxels<__half> {
   uint32_t c[4];
 };
 
-// Load the 8 voxels around a sample point.  Byte offsets from the brick base:
-// 32-bit sums of per-axis terms for bricks below 4 GiB; WIDE (the blocked array is
-// 4 GiB or more, or 64-bit offsets were asked for): 32-bit element indices (a
-// brick holds fewer than 2^32 elements), widened and scaled once per load.
-// Either way the loads are global loads.  An FP16 brick is stored as voxel pairs
-// when addressed with 32-bit offsets and as 2-byte voxels when addressed with
-// 64-bit offsets (the commit picks the layout and the addressing together).
-template <typename T, bool WIDE>
-__device__ __forceinline__ void load_voxels(const SceneG& sc, const BrickG& b, const int64_t p[3], Voxels<T>& g) {
-  const int lx = axis_index(p[0], sc.dims[0], b.slo[0], b.sdim[0]);
-  const int ly = axis_index(p[1], sc.dims[1], b.slo[1], b.sdim[1]);
-  const int lz = axis_index(p[2], sc.dims[2], b.slo[2], b.sdim[2]);
+// Load the 8 voxels around base voxel (lx, ly, lz) (stored indices).  Byte offsets from
+// the brick base: 32-bit sums for bricks below 4 GiB; WIDE (the blocked array is 4 GiB
+// or more, or 64-bit offsets were asked for): 32-bit element indices (a brick holds
+// fewer than 2^32 elements), widened and scaled once per load.  Either way the loads
+// are global loads.  An FP16 brick is stored as voxel pairs when addressed with 32-bit
+// offsets and as 2-byte voxels when addressed with 64-bit offsets (the commit picks
+// the layout and the addressing together).
+template <typename T, bool WIDE, bool UNI>
+__device__ __forceinline__ void load_footprint(const BrickG& b, int lx, int ly, int lz, Voxels<T>& g) {
   using GC = const char __attribute__((address_space(1)))*;
   if constexpr (sizeof(T) == 4) {
-    constexpr int SH = 2;
-    uint32_t x0, x1, y0, y1, z0, z1;
-    if constexpr (WIDE) {
-      x0 = blk_x(lx), x1 = blk_x(lx + 1);
-      y0 = blk_y(ly, b.bsy), y1 = blk_y(ly + 1, b.bsy);
-      z0 = blk_z(lz, b.bsz), z1 = blk_z(lz + 1, b.bsz);
-    } else {
-      const uint32_t bsy = b.bsy << SH, bsz = b.bsz << SH;
-      x0 = blkb_x<SH>(lx), x1 = blkb_x<SH>(lx + 1);
-      y0 = blkb_y<SH>(ly, bsy), y1 = blkb_y<SH>(ly + 1, bsy);
-      z0 = blkb_z<SH>(lz, bsz), z1 = blkb_z<SH>(lz + 1, bsz);
-    }
+    constexpr int SH = WIDE ? 0 : 2;
+    const Foot f = footprint<SH, UNI>(b, lx, ly, lz, in_block_x(lx));
     // byte offset of the element at the sum of the per-axis terms
     auto off = [](uint32_t e) {
       if constexpr (WIDE)
-        return (uint64_t)e << SH;
+        return (uint64_t)e << 2;
       else
         return e;
     };
-    const uint32_t a00 = x0 + y0, a01 = x0 + y1;
+    const uint32_t a0 = f.a, a1 = f.a + f.dy, a2 = f.a + f.dz, a3 = a2 + f.dy;
     // voxel lx + 1 follows voxel lx in memory unless lx ends a 4-voxel x-run, so
     // each x-pair is one 8-byte load; lanes at a run's end read lx + 1 on their
     // own.
-    const float2 c0 = load_pair_f32(b.data, off(a00 + z0)), c1 = load_pair_f32(b.data, off(a01 + z0));
-    const float2 c2 = load_pair_f32(b.data, off(a00 + z1)), c3 = load_pair_f32(b.data, off(a01 + z1));
+    const float2 c0 = load_pair_f32(b.data, off(a0)), c1 = load_pair_f32(b.data, off(a1));
+    const float2 c2 = load_pair_f32(b.data, off(a2)), c3 = load_pair_f32(b.data, off(a3));
     g.v[0] = c0.x;
     g.v[1] = c0.y;
     g.v[2] = c1.x;
@@ -190,52 +140,55 @@ __device__ __forceinline__ void load_voxels(const SceneG& sc, const BrickG& b, c
     g.v[6] = c3.x;
     g.v[7] = c3.y;
     if ((lx & 3) == 3) {
-      const uint32_t a10 = x1 + y0, a11 = x1 + y1;
-      g.v[1] = load_voxel_b<T>(b.data, off(a10 + z0));
-      g.v[3] = load_voxel_b<T>(b.data, off(a11 + z0));
-      g.v[5] = load_voxel_b<T>(b.data, off(a10 + z1));
-      g.v[7] = load_voxel_b<T>(b.data, off(a11 + z1));
+      // from element 3 of a run to the block's second run, or to the next block
+      const uint32_t dx = (lx & 4) ? (512u - 67u) << SH : (64u - 3u) << SH;
+      g.v[1] = load_voxel_b<T>(b.data, off(a0 + dx));
+      g.v[3] = load_voxel_b<T>(b.data, off(a1 + dx));
+      g.v[5] = load_voxel_b<T>(b.data, off(a2 + dx));
+      g.v[7] = load_voxel_b<T>(b.data, off(a3 + dx));
     }
   } else if constexpr (WIDE) {
     // FP16 voxels (2 bytes: the layout of bricks addressed with 64-bit offsets):
     // the aligned 4-voxel run holding lx is one 8-byte load and the pair
     // (lx, lx + 1) is shifted out of it; lanes whose lx ends a run read lx + 1 on
-    // their own.  Element offsets are 32-bit sums (a brick holds fewer than 2^32
-    // elements), widened and scaled once per load.
+    // their own.
     using GU64 = const uint64_t __attribute__((address_space(1)))*;
     using GU16 = const uint16_t __attribute__((address_space(1)))*;
-    const uint32_t y0 = blk_y(ly, b.bsy), y1 = blk_y(ly + 1, b.bsy);
-    const uint32_t z0 = blk_z(lz, b.bsz), z1 = blk_z(lz + 1, b.bsz);
-    const uint32_t x0 = blk_x(lx & ~3);
+    const Foot f = footprint<0, UNI>(b, lx, ly, lz, ((uint32_t)lx & 4u) << 4);
     auto off = [](uint32_t e) { return (uint64_t)e << 1; };
-    const uint32_t a00 = x0 + y0, a01 = x0 + y1;
+    const uint32_t a0 = f.a, a1 = f.a + f.dy, a2 = f.a + f.dz, a3 = a2 + f.dy;
     const uint32_t rs = (uint32_t)(lx & 3) << 4;
-    g.c[0] = (uint32_t)(*(GU64)((GC)b.data + off(a00 + z0)) >> rs);
-    g.c[1] = (uint32_t)(*(GU64)((GC)b.data + off(a01 + z0)) >> rs);
-    g.c[2] = (uint32_t)(*(GU64)((GC)b.data + off(a00 + z1)) >> rs);
-    g.c[3] = (uint32_t)(*(GU64)((GC)b.data + off(a01 + z1)) >> rs);
+    g.c[0] = (uint32_t)(*(GU64)((GC)b.data + off(a0)) >> rs);
+    g.c[1] = (uint32_t)(*(GU64)((GC)b.data + off(a1)) >> rs);
+    g.c[2] = (uint32_t)(*(GU64)((GC)b.data + off(a2)) >> rs);
+    g.c[3] = (uint32_t)(*(GU64)((GC)b.data + off(a3)) >> rs);
     if ((lx & 3) == 3) {
-      const uint32_t x1 = blk_x(lx + 1), a10 = x1 + y0, a11 = x1 + y1;
-      g.c[0] = (g.c[0] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a10 + z0)) << 16);
-      g.c[1] = (g.c[1] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a11 + z0)) << 16);
-      g.c[2] = (g.c[2] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a10 + z1)) << 16);
-      g.c[3] = (g.c[3] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a11 + z1)) << 16);
+      // from the run's start to the block's second run, or to the next block
+      const uint32_t dx = (lx & 4) ? 512u - 64u : 64u;
+      g.c[0] = (g.c[0] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a0 + dx)) << 16);
+      g.c[1] = (g.c[1] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a1 + dx)) << 16);
+      g.c[2] = (g.c[2] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a2 + dx)) << 16);
+      g.c[3] = (g.c[3] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a3 + dx)) << 16);
     }
   } else {
     // FP16 voxel pairs (4 bytes, the layout of bricks below 4 GiB): each element
     // holds the voxels (x, x + 1), one aligned 4-byte load per pair
-    constexpr int SH = 2;
     using GU = const uint32_t __attribute__((address_space(1)))*;
-    const uint32_t bsy = b.bsy << SH, bsz = b.bsz << SH;
-    const uint32_t x0 = blkb_x<SH>(lx);
-    const uint32_t y0 = blkb_y<SH>(ly, bsy), y1 = blkb_y<SH>(ly + 1, bsy);
-    const uint32_t z0 = blkb_z<SH>(lz, bsz), z1 = blkb_z<SH>(lz + 1, bsz);
-    const uint32_t a00 = x0 + y0, a01 = x0 + y1;
-    g.c[0] = *(GU)((GC)b.data + a00 + z0);
-    g.c[1] = *(GU)((GC)b.data + a01 + z0);
-    g.c[2] = *(GU)((GC)b.data + a00 + z1);
-    g.c[3] = *(GU)((GC)b.data + a01 + z1);
+    const Foot f = footprint<2, UNI>(b, lx, ly, lz, in_block_x(lx));
+    const uint32_t a2 = f.a + f.dz;
+    g.c[0] = *(GU)((GC)b.data + f.a);
+    g.c[1] = *(GU)((GC)b.data + (f.a + f.dy));
+    g.c[2] = *(GU)((GC)b.data + a2);
+    g.c[3] = *(GU)((GC)b.data + (a2 + f.dy));
   }
+}
+
+// Load the 8 voxels around a sample point.
+template <typename T, bool WIDE>
+__device__ __forceinline__ void load_voxels(const SceneG& sc, const BrickG& b, const int64_t p[3], Voxels<T>& g) {
+  load_footprint<T, WIDE, false>(b, axis_index(p[0], sc.dims[0], b.slo[0], b.sdim[0]),
+                                 axis_index(p[1], sc.dims[1], b.slo[1], b.sdim[1]),
+                                 axis_index(p[2], sc.dims[2], b.slo[2], b.sdim[2]), g);
 }
 
 // The 8 footprint voxels as FP32: (x0, x1) at (y0, z0), (y1, z0), (y0, z1), (y1, z1).
@@ -278,79 +231,201 @@ __device__ __forceinline__ float trilerp(const Gather<T>& g) {
   return fmaf(g.fz, c1 - c0, c0);
 }
 
-// Shade one sample of value v; returns true when the ray terminates early.
-__device__ __forceinline__ bool shade_v(const SceneG& sc, const float4* __restrict__ tfb,
-                                        const float4* __restrict__ tfs, float v, float Dl, double& tau_acc,
-                                        float& tr, float& cr, float& cg, float& cb) {
-  float x = (v - sc.tf_lo) * sc.tf_scale;
-  x = fminf(fmaxf(x, 0.f), (float)(sc.ntf - 1));
-  const int j = min((int)x, sc.ntf - 2);
-  const float w = x - (float)j;
-  const float4 tb = tfb[j], ts = tfs[j];
-  const float A = fmaf(w, ts.w, tb.w);
-  const float tau = Dl * A;
-  if (tau > 0.f) {
-    tau_acc += (double)tau;
-    const float tn = __expf(-(float)tau_acc);
-    const float wgt = tr - tn;
-    cr = fmaf(wgt, fmaf(w, ts.x, tb.x), cr);
-    cg = fmaf(wgt, fmaf(w, ts.y, tb.y), cg);
-    cb = fmaf(wgt, fmaf(w, ts.z, tb.z), cb);
-    tr = tn;
-    return 1.f - tr >= sc.ert;
-  }
-  return false;
+
+// ---------------------------------------------------------------- the march
+// L lanes per ray, one or the four of a DPP quad; each takes every L-th sample.
+//
+// A ray is a serial chain: with one lane per ray a launch takes at least its longest
+// ray's samples times the time a wave needs for one, and its last rays leave most of
+// the chip idle.  With four lanes the chain is a quarter as long, and a wave's loads
+// cover 16 rays over two voxels of depth, which is fewer cache lines than 64 rays at
+// one depth.  Per four samples the lanes gather, interpolate and look up their own
+// one; what is serial -- the optical depth and the colour sums -- then runs in sample
+// order in every lane of the quad on broadcast values, so one and four lanes give the
+// same bits.  The batched renderer uses four lanes (times in k_batch.hip), the plain
+// launch, which also counts a ray's samples, one.
+//
+// The lattice is walked in trips of R steps of L samples.  A gather buffer per step in
+// flight, the next NB - 1 steps' voxels requested ahead; the majorant of the next
+// trip's first samples is requested with them.  If every lane's next sample lies in an
+// empty macrocell the steps that all of them make inside their own are skipped (a
+// sample of zero opacity changes nothing, so any part of a run may be skipped or
+// sampled with the same bits).  Steps past a ray's last segment, or after it ended,
+// have length 0, which leaves every sum as it is, so a trip's body has no exits.
+//
+// Every branch condition is the same in the lanes of a ray.
+constexpr int kRayDone = -(1 << 29);  // LaneRay::m of a ray that ended early
+
+template <int L>
+struct LaneCfg {
+  static constexpr int NB = 2, R = L == 4 ? 2 : 4;
+  static constexpr int kTrips = 128 / (R * L);  // between refill checks: at most 128 samples of a ray
+};
+
+struct LaneRay {
+  int64_t q[3];  // this lane's next sample point, 32.32 fixed point, in stored voxel indices of the brick
+  int64_t d[3];  // advance of L segments
+  double acc;    // optical depth before the next L samples
+  float tr;      // transmittance after this lane's last sample (the last lane's: after the last L samples)
+  float cr, cg, cb;
+  float dl_cur, dl_last;  // D * length of this lane's next segment unless it is the ray's last / of the last
+  float t_in;
+  int m;         // last segment minus this lane's next one
+  int n;         // (one lane) logical samples processed, once the ray has ended
+  float pv;      // iso-surfaces: value of the sample before q
+  int pst;       // iso-surfaces: bit 0 side of that sample, bit 1 the next sample closes a tested
+                 // pair, bit 2 pv holds the value
+};
+
+template <int CTRL>
+__device__ __forceinline__ float quad_perm(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ int quad_perm(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+template <int K>
+__device__ __forceinline__ float quad_bcast(float v) {
+  return quad_perm<K * 0x55>(v);
+}
+template <int K>
+__device__ __forceinline__ double quad_bcast(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)quad_perm<K * 0x55>((int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)quad_perm<K * 0x55>((int)(uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ float masked(float v, int mask) { return __int_as_float(__float_as_int(v) & mask); }
+__device__ __forceinline__ float quad_max(float v) {
+  v = fmaxf(v, quad_perm<0xB1>(v));
+  return fmaxf(v, quad_perm<0x4E>(v));
+}
+__device__ __forceinline__ int quad_min(int v) {
+  v = min(v, quad_perm<0xB1>(v));
+  return min(v, quad_perm<0x4E>(v));
 }
 
+// min(max(i, 0), top) for a wave-uniform top >= 0
+__device__ __forceinline__ int clamp_index(int i, int top) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(i), "s"(top));
+  return r;
+}
+
+// Base voxel and fraction along one axis of a point in stored voxel indices, clamped
+// to the stored range [0, top + 1] (top = stored extent - 2).  The commit guarantees
+// that a ray's own samples leave the stored range only through a global face, where
+// this is the clamp of the sampling rule.
+__device__ __forceinline__ int local_axis(int64_t p, int top, float& f) {
+  const int hi = (int)(p >> 32);
+  const int i = clamp_index(hi, top);
+  // i == hi: the fraction; hi below or above the range: 0 or 1
+  f = __builtin_amdgcn_fmed3f(fmaf((float)(uint32_t)p, 1.0f / 4294967296.0f, (float)(hi - i)), 0.f, 1.f);
+  return i;
+}
+
+// A requested sample: its voxels and trilinear fractions.
 template <typename T>
-__device__ __forceinline__ bool shade(const SceneG& sc, const float4* __restrict__ tfb,
-                                      const float4* __restrict__ tfs, const Gather<T>& g, float Dl, double& tau_acc,
-                                      float& tr, float& cr, float& cg, float& cb) {
-  return shade_v(sc, tfb, tfs, trilerp(g), Dl, tau_acc, tr, cr, cg, cb);
+struct Sample {
+  Voxels<T> v;
+  float fx, fy, fz;
+};
+
+// Interpolate a requested sample (the lerps of trilerp).  FP16: the difference of a
+// pair's halves is one mixed-precision FMA, exact like the FP32 difference of the
+// converted halves, and the halves themselves are FMA operands.
+__device__ __forceinline__ float pair_diff(uint32_t c) {
+  float d;
+  asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(c));
+  return d;
+}
+__device__ __forceinline__ float lerp_yz(float c00, float c01, float c10, float c11, float fy, float fz) {
+  const float c0 = fmaf(fy, c01 - c00, c00), c1 = fmaf(fy, c11 - c10, c10);
+  return fmaf(fz, c1 - c0, c0);
+}
+__device__ __forceinline__ float sample_value(const Sample<float>& s) {
+  const float* v = s.v.v;
+  return lerp_yz(fmaf(s.fx, v[1] - v[0], v[0]), fmaf(s.fx, v[3] - v[2], v[2]), fmaf(s.fx, v[5] - v[4], v[4]),
+                 fmaf(s.fx, v[7] - v[6], v[6]), s.fy, s.fz);
+}
+__device__ __forceinline__ float sample_value(const Sample<__half>& s) {
+  auto lerp_x = [&](uint32_t c) {
+    return fmaf(s.fx, pair_diff(c), __half2float(__ushort_as_half((unsigned short)(c & 0xffffu))));
+  };
+  return lerp_yz(lerp_x(s.v.c[0]), lerp_x(s.v.c[1]), lerp_x(s.v.c[2]), lerp_x(s.v.c[3]), s.fy, s.fz);
 }
 
-// Set up the ray (ray_begin) and, for iso-surfaces, the pair at the brick entry:
-// when the first processed segment starts exactly at t_in its lattice point is
-// this brick's, and the sample half a step before the entry opens the pair.
-template <typename T, bool WIDE, bool ISO>
-__device__ __forceinline__ bool ray_start(const SceneG& sc, const BrickG& b, const double o[3], const double d[3],
-                                          RayState& r) {
-  if (!ray_begin(sc, b, o, d, r)) return false;
+// Request the 8 voxels around a point in stored voxel indices of a wave-uniform brick.
+template <typename T, bool WIDE>
+__device__ __forceinline__ void request(const BrickG& b, int64_t x, int64_t y, int64_t z, Sample<T>& g) {
+  const int lx = local_axis(x, b.sdim[0] - 2, g.fx);
+  const int ly = local_axis(y, b.sdim[1] - 2, g.fy);
+  const int lz = local_axis(z, b.sdim[2] - 2, g.fz);
+  load_footprint<T, WIDE, true>(b, lx, ly, lz, g.v);
+}
+
+// Set up lane k's part of a ray: ray_begin, then the points of segments s0 + k,
+// s0 + k + L, ... relative to the brick's first stored voxel (exact integers).  For
+// iso-surfaces, the pair at the brick entry: when the first processed segment starts
+// exactly at t_in its lattice point is this brick's, and the sample half a step before
+// the entry opens the pair.
+template <typename T, bool WIDE, bool ISO, int L>
+__device__ __forceinline__ bool lane_begin(const SceneG& sc, const BrickG& b, const double o[3], const double d[3],
+                                           int k, LaneRay& r) {
+  RaySetup f;
+  if (!ray_begin(sc, b, o, d, f)) return false;
+  int64_t p[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    p[a] = f.p[a] - ((int64_t)b.slo[a] << 32);
+    r.q[a] = p[a] + (int64_t)k * f.dp[a];
+    r.d[a] = L * f.dp[a];
+  }
+  r.acc = 0.0;
+  r.tr = 1.f;
+  r.cr = r.cg = r.cb = 0.f;
+  r.t_in = (float)f.t_in;
+  r.m = f.s1 - f.s0 - k;
+  r.n = f.s1 - f.s0 + 1;
+  r.dl_cur = k == 0 ? f.dl_first : sc.density * sc.dt_f;
+  r.dl_last = f.s0 == f.s1 ? f.dl_first : f.dl_last;
   if constexpr (ISO) {
     r.pv = 0.f;
     r.pst = 0;
-    if ((double)r.s0 * sc.dt >= r.t_in) {
-      const int64_t q[3] = {r.p[0] - r.dp[0], r.p[1] - r.dp[1], r.p[2] - r.dp[2]};
-      Gather<T> g;
-      gather<T, WIDE>(sc, b, q, g);
-      r.pv = trilerp(g);
+    if ((double)f.s0 * sc.dt >= f.t_in) {
+      Sample<T> s;
+      request<T, WIDE>(b, p[0] - f.dp[0], p[1] - f.dp[1], p[2] - f.dp[2], s);
+      r.pv = sample_value(s);
       r.pst = kIsoPair | kIsoKnown | (r.pv >= sc.iso ? kIsoSide : 0);
     }
   }
   return true;
 }
 
-// The opaque surface between samples s - 1 and s (value vs; q: the fixed-point
-// point of sample s): crossing by linear interpolation, normal = gradient of the
-// trilinear patch there, colour = TF colour at v_iso * (k_a + k_d |cos|).
+// The opaque surface between samples s - 1 and s (value vs; q: the point of sample s,
+// dq: advance per segment): crossing by linear interpolation, normal = gradient of the
+// trilinear patch there, colour = TF colour at v_iso * (k_a + k_d |cos|).  Adds it to
+// the colour behind transmittance tr.
 template <typename T, bool WIDE>
-__device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const float4* __restrict__ tfb,
-                                     const float4* __restrict__ tfs, const int64_t q[3], const int64_t dq[3],
-                                     float vs, int pst, float pv, float& tr, float& cr, float& cg, float& cb) {
+__device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const float4* tfr, const int64_t q[3],
+                                        const int64_t dq[3], float vs, int pst, float pv, float tr, float& cr,
+                                        float& cg, float& cb) {
   const int64_t qp[3] = {q[0] - dq[0], q[1] - dq[1], q[2] - dq[2]};
   float vp = pv;
   if (!(pst & kIsoKnown)) {  // the previous sample was skipped: its value now
-    Gather<T> g;
-    gather<T, WIDE>(sc, b, qp, g);
-    vp = trilerp(g);
+    Sample<T> g;
+    request<T, WIDE>(b, qp[0], qp[1], qp[2], g);
+    vp = sample_value(g);
   }
   const float f = (sc.iso - vp) / (vs - vp);
   int64_t qh[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) qh[a] = qp[a] + __double2ll_rn((double)f * (double)dq[a]);
-  Gather<T> g;
-  gather<T, WIDE>(sc, b, qh, g);
-  const float* v = g.v;
+  Sample<T> g;
+  request<T, WIDE>(b, qh[0], qh[1], qh[2], g);
+  float v[8];
+  decode_voxels<T>(g.v, v);
   // d/dx, d/dy, d/dz of the patch: the edge differences, interpolated in the other two axes
   const float x0 = fmaf(g.fy, (v[3] - v[2]) - (v[1] - v[0]), v[1] - v[0]);
   const float x1 = fmaf(g.fy, (v[7] - v[6]) - (v[5] - v[4]), v[5] - v[4]);
@@ -374,308 +449,287 @@ __device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const
   x = fminf(fmaxf(x, 0.f), (float)(sc.ntf - 1));
   const int j = min((int)x, sc.ntf - 2);
   const float w = x - (float)j;
-  const float4 tb = tfb[j], ts = tfs[j];
+  const float4 tb = tfr[2 * j], ts = tfr[2 * j + 1];
   const float lit = fmaf(sc.iso_kd, fminf(cosv, 1.f), sc.iso_ka);
   cr = fmaf(tr, __fmul_rn(fmaf(w, ts.x, tb.x), lit), cr);
   cg = fmaf(tr, __fmul_rn(fmaf(w, ts.y, tb.y), lit), cg);
   cb = fmaf(tr, __fmul_rn(fmaf(w, ts.z, tb.z), lit), cb);
-  tr = 0.f;
 }
 
-// Emission-absorption march (no iso-surface) with a deeper pipeline: the voxels
-// of the next two samples are in flight while a sample is shaded, and the
-// majorant of the next run's macrocell is requested at the start of a run, so a
-// lane waits on memory about once per sample rather than once per sample plus
-// once per run.  Three gather buffers rotate; a run of a multiple of three
-// samples leaves the two buffers after it holding the next run's first two
-// samples.  Same lattice points, the same skip decisions, the same shading
-// order and the same termination test as the single-lookahead loop, so the
-// same bits.
-constexpr int kPipeRun = 6;  // samples per run in a non-empty macrocell (a multiple of 3)
-
-template <typename T, bool SKIP, bool WIDE>
-__device__ __forceinline__ bool ray_advance_ea(const SceneG& sc, const BrickG& b, const float4* __restrict__ tfb,
-                                               const float4* __restrict__ tfs, RayState& r, int budget,
-                                               int min_lanes) {
+// March until the ray ends (true), max_trips trips have passed, or fewer than
+// min_lanes lanes of the wave are still marching.  b is wave-uniform.
+template <typename T, bool SKIP, bool WIDE, bool ISO, int L>
+__device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, const float4* tfr, LaneRay& r,
+                                             int max_trips, int min_lanes) {
+  static_assert(L == 1 || L == 4, "one lane, or a DPP quad");
+  constexpr int NB = LaneCfg<L>::NB, R = LaneCfg<L>::R;
+  static_assert(R % NB == 0 && NB >= 2, "a trip ends with the buffers as it found them");
+  const int lane = threadIdx.x & 63, k = lane & (L - 1);
+  const int from1 = k >= 1 ? -1 : 0, from2 = k >= 2 ? -1 : 0, from3 = k >= 3 ? -1 : 0;
+  const float x_max = (float)(sc.ntf - 1);
   const float Ddt = sc.density * sc.dt_f;
-  const int64_t half = 0x80000000ll;
-  int s = r.s;
-  int n = r.n;
-  int64_t p0 = r.p[0], p1 = r.p[1], p2 = r.p[2];
-  const int64_t d0 = r.dp[0], d1 = r.dp[1], d2 = r.dp[2];
-  float tr = r.T, cr = r.cr, cg = r.cg, cb = r.cb;
-  double tau_acc = r.tau;
-  bool done = false;
-  Voxels<T> ga, gb, gc;
-  bool pre = false;      // ga, gb hold the voxels of samples s and s + 1
-  int64_t q0 = 0, q1 = 0, q2 = 0;  // point of the next sample to request
-  float mj_next = 0.f;
-  bool have_mj = false;  // mj_next is the majorant of sample s's macrocell
-  auto macrocell = [&](int64_t x, int64_t y, int64_t z, int m[3]) {
-    const int64_t pp[3] = {x, y, z};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int cell = (int)((pp[a] + half) >> 32);
-      m[a] = min(max((cell - b.olo[a]) >> b.mc_shift, 0), b.mdim[a] - 1);
-    }
-  };
-  auto majorant = [&](const int m[3]) { return ld_global(b.majorant, (m[2] * b.mdim[1] + m[1]) * b.mdim[0] + m[0]); };
-  auto request = [&](Voxels<T>& g) {
-    const int64_t q[3] = {q0, q1, q2};
-    load_voxels<T, WIDE>(sc, b, q, g);
-    q0 += d0;
-    q1 += d1;
-    q2 += d2;
-  };
-  // shade sample s from its voxels; its fractions come from its point, p
-  auto step = [&](const Voxels<T>& g) -> bool {
-    Gather<T> gg;
-    const int64_t pc[3] = {p0, p1, p2};
-    sample_frac(sc, pc, gg.fx, gg.fy, gg.fz);
-    decode_voxels<T>(g, gg.v);
-    const float Dl = (s == r.s0) ? r.dl_first : ((s == r.s1) ? r.dl_last : Ddt);
-    ++n;
-    ++s;
-    p0 += d0;
-    p1 += d1;
-    p2 += d2;
-    return shade<T>(sc, tfb, tfs, gg, Dl, tau_acc, tr, cr, cg, cb);
-  };
-  while (!done && s <= r.s1 && budget > 0) {
-    // at a run boundary: return early (unfinished) once fewer than min_lanes lanes
-    // of the wave are still marching, so the caller can refill the idle ones
-    if (__popcll(__ballot(1)) < min_lanes) break;
-    int run = min(r.s1 - s + 1, budget);
-    if constexpr (SKIP) {
-      int m[3];
-      macrocell(p0, p1, p2, m);
-      const float mj = have_mj ? mj_next : majorant(m);
-      if (mj == 0.f) {
-        // exactly the samples left inside this empty macrocell (outer cells
-        // unbounded); every one has opacity exactly 0
-        const int64_t pp[3] = {p0, p1, p2}, dd[3] = {d0, d1, d2};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const int ma = m[a];
-          const int64_t blo = (ma == 0) ? INT64_MIN
-                                        : ((int64_t)(b.olo[a] + (ma << b.mc_shift)) << 32) - half;
-          const int64_t bhi = (ma == b.mdim[a] - 1) ? INT64_MAX
-                                                    : ((int64_t)(b.olo[a] + ((ma + 1) << b.mc_shift)) << 32) - half;
-          run = min(run, 1 + steps_inside(pp[a], dd[a], blo, bhi, run - 1));
-        }
-        s += run;
-        n += run;
-        budget -= run;
-        p0 += (int64_t)run * d0;
-        p1 += (int64_t)run * d1;
-        p2 += (int64_t)run * d2;
-        pre = false;
-        have_mj = false;
-        continue;
-      }
-      // a non-empty macrocell: a fixed number of samples, then look again (the
-      // run may cross into other macrocells; a sample of zero opacity changes
-      // nothing, so its length needs no exact boundary arithmetic)
-      run = min(run, kPipeRun);
-      int mn[3];
-      macrocell(p0 + (int64_t)run * d0, p1 + (int64_t)run * d1, p2 + (int64_t)run * d2, mn);
-      mj_next = majorant(mn);
-      have_mj = true;
-    }
-    budget -= run;
-    if (!pre) {
-      q0 = p0;
-      q1 = p1;
-      q2 = p2;
-      request(ga);
-      request(gb);
-    }
-    // the request two samples ahead is unconditional (past the run's last sample
-    // it reads clamped, in-brick voxels that are never used).  Three buffers
-    // rotate by position (no register copies: copying a buffer whose load is in
-    // flight would wait for it), and the loop body has no exit: a step past the
-    // run's end or after termination is skipped, not left, which keeps the
-    // control flow simple enough for the buffers to stay in place
-    for (int i = 0; i < run; i += 3) {
-      request(gc);
-      if (!done) done = step(ga);
-      request(ga);
-      if (!done && i + 1 < run) done = step(gb);
-      request(gb);
-      if (!done && i + 2 < run) done = step(gc);
-    }
-    pre = !done && run % 3 == 0;
-  }
-  // the fixed-point position always corresponds to segment s
-  r.s = s;
-  r.p[0] = p0;
-  r.p[1] = p1;
-  r.p[2] = p2;
-  r.T = tr;
-  r.cr = cr;
-  r.cg = cg;
-  r.cb = cb;
-  r.tau = tau_acc;
-  r.n = n;
-  return done || s > r.s1;
-}
-
-// Advance by at most `budget` lattice segments.  Returns true once the ray is
-// finished: past its last segment, or terminated early (1 - T >= ert, tested
-// after every segment that changed T).
-template <typename T, bool SKIP, bool WIDE, bool ISO>
-__device__ __forceinline__ bool ray_advance(const SceneG& sc, const BrickG& b, const float4* __restrict__ tfb,
-                                            const float4* __restrict__ tfs, RayState& r, int budget,
-                                            int min_lanes = 0) {
-  if constexpr (!ISO) return ray_advance_ea<T, SKIP, WIDE>(sc, b, tfb, tfs, r, budget, min_lanes);
-  const float Ddt = sc.density * sc.dt_f;
-  int s = r.s;
-  int n = r.n;
-  int64_t p0 = r.p[0], p1 = r.p[1], p2 = r.p[2];
-  const int64_t d0 = r.dp[0], d1 = r.dp[1], d2 = r.dp[2];
-  float tr = r.T, cr = r.cr, cg = r.cg, cb = r.cb;
-  double tau_acc = r.tau;
-  bool done = false;
+  int64_t q0 = r.q[0], q1 = r.q[1], q2 = r.q[2];
+  const int64_t d0 = r.d[0], d1 = r.d[1], d2 = r.d[2];
+  double acc = r.acc;
+  float tr = r.tr, cr = r.cr, cg = r.cg, cb = r.cb;
+  float dl_cur = r.dl_cur;
+  int m = r.m;
   int pst = ISO ? r.pst : 0;
   float pv = ISO ? r.pv : 0.f, vh = 0.f;
-  bool hit = false;
-  // ga holds the voxels of the current sample point when pre is set: a run of even
-  // length ends with the next sample's gather in ga, and the next run reuses it
-  Gather<T> ga, gb;
-  bool pre = false;
-  while (!done && s <= r.s1 && budget > 0) {
-    // at a run boundary: return early (unfinished) once fewer than min_lanes lanes
-    // of the wave are still marching, so the caller can refill the idle ones
-    if (__popcll(__ballot(1)) < min_lanes) break;
-    int run = min(r.s1 - s + 1, budget);
-    bool empty = false;
-    if (SKIP) {
-      // macrocell of the current sample point: cell = floor(g + 1/2)
-      const int64_t half = 0x80000000ll;
-      const int64_t pp[3] = {p0, p1, p2};
-      int m[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const int cell = (int)((pp[a] + half) >> 32);
-        m[a] = min(max((cell - b.olo[a]) >> b.mc_shift, 0), b.mdim[a] - 1);
+  int hit = -1;  // iso-surfaces: L * (step of the trip) + (lane of the ray) of the sample behind the surface
+
+  // the next L samples, in order; i: step of the trip
+  auto step = [&](const Sample<T>& s, int i) {
+    const float v = sample_value(s);
+    const float x = __builtin_amdgcn_fmed3f((v - sc.tf_lo) * sc.tf_scale, 0.f, x_max);
+    const int j = min((int)x, sc.ntf - 2);
+    const float w = x - (float)j;
+    const float4 tb = tfr[2 * j], ts = tfr[2 * j + 1];
+    float Dl = m > 0 ? dl_cur : (m == 0 ? r.dl_last : 0.f);
+    dl_cur = Ddt;
+    int surf = L;  // lane of the first sample behind the surface
+    if constexpr (ISO) {
+      // a change of side against the sample before ends the ray on the surface
+      const int side = v >= sc.iso ? kIsoSide : 0;
+      int prev = pst;
+      if constexpr (L == 4) {
+        const int ps = quad_perm<0x90>(side);
+        prev = k == 0 ? pst : (ps | kIsoPair);
       }
-      const float mj = ld_global(b.majorant, (m[2] * b.mdim[1] + m[1]) * b.mdim[0] + m[0]);
-      if constexpr (ISO) {
-        empty = mj <= 0.f && (!(pst & kIsoPair) || ((mj < 0.f) == (bool)(pst & kIsoSide)));
-        if (empty) pst = kIsoPair | (mj < 0.f ? kIsoSide : 0);
-      } else {
-        empty = mj == 0.f;
+      const bool cross = m >= 0 && (prev & kIsoPair) && side != (prev & kIsoSide);
+      bool hit_now = cross;
+      if constexpr (L == 4) {
+        const uint64_t cm = __ballot(cross);
+        const uint32_t nib = cm ? (uint32_t)(cm >> (lane & 60)) & 15u : 0u;
+        hit_now = nib != 0;
+        if (hit_now) surf = __ffs(nib) - 1;
       }
-      if (empty) {
-        // exactly the samples left inside this empty macrocell (outer cells unbounded)
-        const int64_t dd[3] = {d0, d1, d2};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const int ma = m[a];
-          const int64_t blo = (ma == 0) ? INT64_MIN
-                                        : ((int64_t)(b.olo[a] + (ma << b.mc_shift)) << 32) - half;
-          const int64_t bhi = (ma == b.mdim[a] - 1) ? INT64_MAX
-                                                    : ((int64_t)(b.olo[a] + ((ma + 1) << b.mc_shift)) << 32) - half;
-          run = min(run, 1 + steps_inside(pp[a], dd[a], blo, bhi, run - 1));
-        }
-      } else {
-        // a non-empty macrocell: a fixed number of samples, then look again.  The
-        // run may cross into other macrocells; shading is correct everywhere (a
-        // sample of zero opacity changes nothing), so its length needs no exact
-        // boundary arithmetic and the lanes of a wave stay in step
-        run = min(run, kShadeRun);
-      }
-    }
-    if (empty) {  // every sample in the run has opacity exactly 0
-      s += run;
-      n += run;
-      budget -= run;
-      p0 += (int64_t)run * d0;
-      p1 += (int64_t)run * d1;
-      p2 += (int64_t)run * d2;
-      pre = false;
-      continue;
-    }
-    budget -= run;
-    // one sample per step, the next sample's voxels requested before this one is
-    // shaded; two steps per trip alternate the gather buffers (no register copies).
-    // The request is unconditional (past the run's last sample it reads clamped,
-    // in-brick voxels that are never used), so the wait before shading covers only
-    // the older request.
-    auto step = [&](const Gather<T>& g) -> bool {
-      const float Dl = (s == r.s0) ? r.dl_first : ((s == r.s1) ? r.dl_last : Ddt);
-      ++n;
-      ++s;
-      if constexpr (ISO) {
-        const float v = trilerp(g);
-        const int side = v >= sc.iso ? kIsoSide : 0;
-        if ((pst & kIsoPair) && side != (pst & kIsoSide)) {  // the surface: no emission from this segment
-          hit = true;
+      if (hit_now) {
+        if constexpr (L == 1) {
+          surf = 0;
           vh = v;
-          return true;
+        } else {
+          vh = __shfl(v, (lane & 60) + surf);
+          const float vb = __shfl(v, (lane & 60) + max(surf - 1, 0));
+          if (surf > 0) {
+            pv = vb;
+            pst |= kIsoKnown;
+          }
         }
-        pst = kIsoPair | kIsoKnown | side;
-        pv = v;
-        return shade_v(sc, tfb, tfs, v, Dl, tau_acc, tr, cr, cg, cb);
-      } else {
-        return shade<T>(sc, tfb, tfs, g, Dl, tau_acc, tr, cr, cg, cb);
+        if (k >= surf) Dl = 0.f;  // no emission from the crossing segment on
+        hit = L * i + surf;
+      } else if (hit < 0) {
+        pst = kIsoPair | kIsoKnown | (L == 4 ? quad_perm<0xFF>(side) : side);
+        pv = L == 4 ? quad_bcast<3>(v) : v;
       }
-    };
+    }
+    m -= L;
+    const float tau = fmaxf(Dl * fmaf(w, ts.w, tb.w), 0.f);
+    const float r0 = fmaf(w, ts.x, tb.x), g0 = fmaf(w, ts.y, tb.y), b0 = fmaf(w, ts.z, tb.z);
+    if constexpr (L == 1) {
+      acc += (double)tau;
+      const float tn = __expf(-(float)acc);
+      const float wgt = tr - tn;
+      tr = tn;
+      cr = fmaf(wgt, r0, cr);
+      cg = fmaf(wgt, g0, cg);
+      cb = fmaf(wgt, b0, cb);
+      const bool end = tn <= sc.ert_t || (ISO && surf == 0);
+      if (end && m > kRayDone / 2) {
+        r.n -= m + 1;
+        m = kRayDone;
+      }
+    } else {
+      // optical depth after this lane's sample, summed in sample order (lanes below a
+      // sample add zero)
+      double a = acc + (double)quad_bcast<0>(tau);
+      a += (double)masked(quad_bcast<1>(tau), from1);
+      a += (double)masked(quad_bcast<2>(tau), from2);
+      a += (double)masked(quad_bcast<3>(tau), from3);
+      float tn = __expf(-(float)a);
+      // transmittance before it: the previous lane's, or what lane 3 left four samples ago
+      float wgt = quad_perm<0x93>(k == 3 ? tr : tn) - tn;
+      const uint64_t term = __ballot(tn <= sc.ert_t);
+      if (term) {  // some ray of the wave ends early: its later samples of these four do not count
+        const uint32_t nib = (uint32_t)(term >> (lane & 60)) & 15u;
+        if (nib) {
+          const int first = __ffs(nib) - 1, src = (lane & 60) + first;
+          if (k > first) wgt = 0.f;
+          a = __shfl(a, src);
+          tn = __shfl(tn, src);
+          m = kRayDone;
+          if (ISO && first < surf && hit >= L * i) hit = -1;  // it ended before the surface
+        }
+      }
+      if (ISO && hit >= 0) m = kRayDone;
+      acc = quad_bcast<3>(a);
+      tr = tn;
+      const float w0 = quad_bcast<0>(wgt), w1 = quad_bcast<1>(wgt), w2 = quad_bcast<2>(wgt), w3 = quad_bcast<3>(wgt);
+      // c = fma(weight, colour, c) in sample order; a DPP operand written by the instruction
+      // before needs two wait states, which the assembler does not add
+      asm("s_nop 1\n\t"
+          "v_fmac_f32_dpp %0, %3, %6 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %1, %4, %6 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %2, %5, %6 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %0, %3, %7 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %1, %4, %7 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %2, %5, %7 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %0, %3, %8 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %1, %4, %8 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %2, %5, %8 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %0, %3, %9 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %1, %4, %9 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %2, %5, %9 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
+          : "+v"(cr), "+v"(cg), "+v"(cb)
+          : "v"(r0), "v"(g0), "v"(b0), "v"(w0), "v"(w1), "v"(w2), "v"(w3));
+    }
+  };
+  // macrocell of a point: cell = floor(g + 1/2), in cells from the brick's first owned one
+  const int64_t c0 = 0x80000000ll - ((int64_t)(b.olo[0] - b.slo[0]) << 32);
+  const int64_t c1 = 0x80000000ll - ((int64_t)(b.olo[1] - b.slo[1]) << 32);
+  const int64_t c2 = 0x80000000ll - ((int64_t)(b.olo[2] - b.slo[2]) << 32);
+  auto macrocell = [&](int64_t cell, int a) {
+    return clamp_index((int)(cell >> 32) >> b.mc_shift, b.mdim[a] - 1);
+  };
+  auto majorant = [&](int64_t x, int64_t y, int64_t z) {
+    const int mx = macrocell(x + c0, 0), my = macrocell(y + c1, 1), mz = macrocell(z + c2, 2);
+    return ld_global(b.majorant, (uint32_t)((mz * b.mdim[1] + my) * b.mdim[0] + mx));
+  };
+  // the samples at the lanes' next points all lie in macrocells that can be skipped
+  auto empty_at = [&](float mj) {
+    if constexpr (ISO) {
+      // transparent, and on the side of the previous sample: classes 0 below, -1 at or above
+      const float hi = L == 4 ? quad_max(mj) : mj, lo = L == 4 ? -quad_max(-mj) : mj;
+      const bool e = hi <= 0.f && lo == hi && (!(pst & kIsoPair) || (hi < 0.f) == (bool)(pst & kIsoSide));
+      if (e) pst = kIsoPair | (hi < 0.f ? kIsoSide : 0);
+      return e;
+    } else {
+      return (L == 4 ? quad_max(mj) : mj) == 0.f;
+    }
+  };
+
+  Sample<T> g[NB];
+  bool pre = false;      // g[0 .. NB - 2] hold the samples at q, q + d, ...
+  float mj_next = 0.f;
+  bool have_mj = false;  // mj_next is the majorant at q
+  bool done = m + k < 0;
+  for (int trip = 0; !done && trip < max_trips; ++trip) {
+    if (__popcll(__ballot(1)) < min_lanes) break;
+    if constexpr (SKIP) {
+      const float mj = have_mj ? mj_next : majorant(q0, q1, q2);
+      if (empty_at(mj)) {
+        // the steps each lane makes inside its own macrocell.  A macrocell's range covers
+        // half a voxel around the samples it holds, so the rounding of these distances
+        // cannot matter.
+        auto steps = [&](int64_t cell, int64_t dd, int a) {
+          const int c = (int)(cell >> 32) - (macrocell(cell, a) << b.mc_shift);
+          const float in = fmaf((float)(uint32_t)cell, 1.0f / 4294967296.0f, (float)c);
+          const float v = fmaf((float)(uint32_t)dd, 1.0f / 4294967296.0f, (float)(int)(dd >> 32));
+          const float dist = v > 0.f ? (float)(1 << b.mc_shift) - in : in;
+          return dist * __builtin_amdgcn_rcpf(fabsf(v));
+        };
+        const float t = fminf(steps(q0 + c0, d0, 0), fminf(steps(q1 + c1, d1, 1), steps(q2 + c2, d2, 2)));
+        int n = 1 + (int)fminf(fmaxf(t, 0.f), (float)(1 << 20));
+        if constexpr (L == 4) n = quad_min(n);
+        n = min(n, (m + k) / L + 1);
+        m -= L * n;
+        dl_cur = Ddt;
+        q0 += (int64_t)n * d0;
+        q1 += (int64_t)n * d1;
+        q2 += (int64_t)n * d2;
+        pre = false;
+        have_mj = false;
+        done = m + k < 0;
+        continue;
+      }
+    }
+    int64_t x = q0, y = q1, z = q2;  // the next point to request
     if (!pre) {
-      const int64_t pc[3] = {p0, p1, p2};
-      gather<T, WIDE>(sc, b, pc, ga);
+#pragma unroll
+      for (int i = 0; i < NB - 1; ++i)
+        request<T, WIDE>(b, q0 + i * d0, q1 + i * d1, q2 + i * d2, g[i]);
     }
-    for (int i = 0;;) {
-      p0 += d0;
-      p1 += d1;
-      p2 += d2;
-      {
-        const int64_t pn[3] = {p0, p1, p2};
-        gather<T, WIDE>(sc, b, pn, gb);
+    x += (NB - 1) * d0;
+    y += (NB - 1) * d1;
+    z += (NB - 1) * d2;
+    int64_t n0 = 0, n1 = 0, n2 = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if (i + NB - 1 == R) {  // the next trip's first samples
+        n0 = x;
+        n1 = y;
+        n2 = z;
+        if constexpr (SKIP) {
+          mj_next = majorant(x, y, z);
+          have_mj = true;
+        }
       }
-      if (step(ga)) {
-        done = true;
-        break;
-      }
-      if (++i >= run) break;
-      p0 += d0;
-      p1 += d1;
-      p2 += d2;
-      {
-        const int64_t pn[3] = {p0, p1, p2};
-        gather<T, WIDE>(sc, b, pn, ga);
-      }
-      if (step(gb)) {
-        done = true;
-        break;
-      }
-      if (++i >= run) break;
+      request<T, WIDE>(b, x, y, z, g[(i + NB - 1) % NB]);
+      // (a chain of additions: left alone, the compiler keeps every multiple of d in registers)
+      x += d0;
+      y += d1;
+      z += d2;
+      asm("" : "+v"(x), "+v"(y), "+v"(z));
+      // (keeps the step's first uses of its voxels, which wait for them, behind the request)
+      __builtin_amdgcn_sched_barrier(0);
+      step(g[i % NB], i);
     }
-    pre = (run & 1) == 0;
+    if (ISO && hit >= 0) {
+      // the point of the sample behind the surface, from this lane's point at the trip's start
+      const int64_t dq[3] = {d0 / L, d1 / L, d2 / L};
+      const int off = hit - k;
+      const int64_t qs[3] = {q0 + off * dq[0], q1 + off * dq[1], q2 + off * dq[2]};
+      const float t_hit = L == 4 ? quad_bcast<3>(tr) : tr;
+      iso_hit<T, WIDE>(sc, b, tfr, qs, dq, vh, pst, pv, t_hit, cr, cg, cb);
+      tr = 0.f;
+    }
+    q0 = n0;
+    q1 = n1;
+    q2 = n2;
+    pre = true;
+    done = m + k < 0;
   }
-  if constexpr (ISO) {
-    if (hit) {  // the hit sample is s - 1, one segment behind the current point
-      const int64_t q[3] = {p0 - d0, p1 - d1, p2 - d2};
-      const int64_t dq[3] = {d0, d1, d2};
-      iso_hit<T, WIDE>(sc, b, tfb, tfs, q, dq, vh, pst, pv, tr, cr, cg, cb);
-    }
-  }
-  // the fixed-point position always corresponds to segment s
-  r.s = s;
-  r.p[0] = p0;
-  r.p[1] = p1;
-  r.p[2] = p2;
-  r.T = tr;
+  r.q[0] = q0;
+  r.q[1] = q1;
+  r.q[2] = q2;
+  r.acc = acc;
+  r.tr = tr;
   r.cr = cr;
   r.cg = cg;
   r.cb = cb;
-  r.tau = tau_acc;
-  r.n = n;
+  r.dl_cur = dl_cur;
+  r.m = m;
   if constexpr (ISO) {
     r.pst = pst;
     r.pv = pv;
   }
-  return done || s > r.s1;
+  return done;
+}
+
+// The table as interleaved (entry, next - entry) records: one LDS address per lookup.
+__device__ __forceinline__ void stage_tf_records(const float4* __restrict__ tf, int ntf, float4* rec, int tid,
+                                                 int nthreads) {
+  for (int i = tid; i < ntf; i += nthreads) {
+    const float4 a = tf[i];
+    const float4 b = (i + 1 < ntf) ? tf[i + 1] : a;
+    rec[2 * i] = a;
+    rec[2 * i + 1] = make_float4(b.x - a.x, b.y - a.y, b.z - a.z, b.w - a.w);
+  }
+}
+
+// Element i (wave-uniform) of an array that no kernel writes, into scalar registers.
+template <typename V>
+__device__ __forceinline__ V ld_uniform(const V* p, int i) {
+  static_assert(sizeof(V) % 4 == 0, "whole words");
+  using C = const uint32_t __attribute__((address_space(4)))*;
+  const C q = (C)(uintptr_t)(p + i);
+  union {
+    uint32_t w[sizeof(V) / 4];
+    V v;
+  } u;
+#pragma unroll
+  for (size_t j = 0; j < sizeof(V) / 4; ++j) u.w[j] = q[j];
+  return u.v;
 }
 
 // Stage the TF as (entry, next - entry) pairs so a lookup is one FMA per channel.

@@ -155,6 +155,13 @@ SceneG make_scene(const dpr_world_t* w) {
   s.dt_f = (float)s.dt;
   s.density = w->density;
   s.ert = w->params.ert_threshold >= 1.f ? 2.f : w->params.ert_threshold;
+  // 1 - T does not increase with T, so the test 1 - T >= ert is T <= ert_t
+  s.ert_t = -1.f;
+  if (s.ert <= 1.f) {
+    s.ert_t = 1.f - s.ert;
+    while (1.f - std::nextafter(s.ert_t, 2.f) >= s.ert) s.ert_t = std::nextafter(s.ert_t, 2.f);
+    while (1.f - s.ert_t < s.ert) s.ert_t = std::nextafter(s.ert_t, -1.f);
+  }
   s.tf_lo = w->tf_lo;
   s.tf_scale = (float)(w->ntf - 1) / (w->tf_hi - w->tf_lo);
   s.ntf = w->ntf;
@@ -179,6 +186,8 @@ BrickG Brick::device_view(bool with_majorant, bool force_wide) const {
   }
   g.bsy = (uint32_t)kBlockVoxels * (uint32_t)bdim[0];
   g.bsz = (uint32_t)kBlockVoxels * (uint32_t)bdim[0] * (uint32_t)bdim[1];
+  g.nbx = (uint32_t)bdim[0];
+  g.nbxy = (uint32_t)bdim[0] * (uint32_t)bdim[1];
   g.majorant = with_majorant ? maj : nullptr;
   // an FP16 brick's addressing follows its layout (2-byte voxels: 64-bit offsets)
   if (dtype == DPR_F16)
