@@ -456,9 +456,11 @@ __device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const
   cb = fmaf(tr, __fmul_rn(fmaf(w, ts.z, tb.z), lit), cb);
 }
 
+// RAW: the table's values are not known to be finite (a sample of no optical depth adds
+// nothing, whatever its colour).
 // March until the ray ends (true), max_trips trips have passed, or fewer than
 // min_lanes lanes of the wave are still marching.  b is wave-uniform.
-template <typename T, bool SKIP, bool WIDE, bool ISO, int L>
+template <typename T, bool SKIP, bool WIDE, bool ISO, int L, bool RAW = false>
 __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, const float4* tfr, LaneRay& r,
                                              int max_trips, int min_lanes) {
   static_assert(L == 1 || L == 4, "one lane, or a DPP quad");
@@ -525,7 +527,8 @@ __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, 
     }
     m -= L;
     const float tau = fmaxf(Dl * fmaf(w, ts.w, tb.w), 0.f);
-    const float r0 = fmaf(w, ts.x, tb.x), g0 = fmaf(w, ts.y, tb.y), b0 = fmaf(w, ts.z, tb.z);
+    float r0 = fmaf(w, ts.x, tb.x), g0 = fmaf(w, ts.y, tb.y), b0 = fmaf(w, ts.z, tb.z);
+    if (RAW && !(tau > 0.f)) r0 = g0 = b0 = 0.f;
     if constexpr (L == 1) {
       acc += (double)tau;
       const float tn = __expf(-(float)acc);

@@ -517,7 +517,13 @@ static void device_drop(dpr_device d) {
   dev_free(d->fix_count);
   dev_free(d->fix_list);
   dev_free(d->comp_prior);
+  // (the training scratch may last have been used on another stream)
+  if (d->train_ev) {
+    (void)hipEventSynchronize(d->train_ev);
+    (void)hipEventDestroy(d->train_ev);
+  }
   dev_free(d->tf_grad64);
+  for (void* p : d->train_buf) dev_free(p);
   delete d;
 }
 

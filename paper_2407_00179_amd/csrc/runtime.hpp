@@ -62,6 +62,13 @@ struct dpr_device_t {
   float* comp_prior = nullptr;  // sampled nearest depth per source (kCompPriorFloats)
   // FP64 sums of the transfer-function gradient across workgroups (dpr_render_backward)
   double* tf_grad64 = nullptr;
+  // blocked copies of the training volume and of its gradient, colours of ray pieces
+  void* train_buf[3] = {nullptr, nullptr, nullptr};
+  size_t train_cap[3] = {0, 0, 0};
+  // last use of the training scratch: an event on the stream it ran on
+  hipEvent_t train_ev = nullptr;
+  hipStream_t train_stream = nullptr;
+  bool train_stream_set = false;
   // device address of the library's fixed scratch array on this GPU
   // (dpr_composite_noalloc), looked up when the handle is created
   void* noalloc_scratch = nullptr;

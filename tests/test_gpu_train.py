@@ -354,3 +354,46 @@ def test_cfg4_per_voxel_finite_differences(gpu_lib, dpr):
             break
     log(f"  cfg4 per-voxel FD: {checked} voxels within {REL_TOL:.0e}")
     assert checked == 64
+
+
+@pytest.mark.parametrize("dims, n_cams, size, step, dist, n_tf, linear", [
+    ((33, 17, 26), 3, (65, 41), 0.5, None, 256, False),      # pieces of quarters, ragged tiles and blocks
+    ((20, 18, 16), 300, (17, 9), 0.25, None, 2, False),      # pieces of tiles, smallest table
+    ((10, 9, 8), 2100, (9, 9), 1.0, None, 1024, False),      # whole rays, largest table
+    ((120, 30, 40), 5, (20, 16), 1.0, None, 256, False),     # patches too wide for whole waves
+    ((24, 25, 31), 4, (30, 27), 0.3, 0.3, 64, False),        # cameras inside: rays of all axes in a wave
+    ((2, 3, 90), 4, (64, 64), 0.4, 0.2, 256, False),         # the thinnest volume
+    ((33, 17, 26), 3, (65, 41), 0.5, None, 256, True),       # no scratch: the linear layout
+    ((20, 18, 16), 3, (24, 20), 0.37, None, 1024, True),
+])
+def test_gradients_over_launch_shapes(gpu_lib, dpr, monkeypatch, dims, n_cams, size, step, dist, n_tf, linear):
+    """Every way the training kernels split their work, against the FP64 oracle."""
+    import ctypes as C
+    dims, vol, tgt_vol, tf, _ = _problem(dims)
+    cams = fibonacci_cameras(dims, n_cams, *size, **({} if dist is None else {"dist": dist}))
+    x = np.linspace(0.0, 1.0, n_tf)
+    tf = np.stack([np.interp(x, np.linspace(0.0, 1.0, len(tf)), tf[:, c]) for c in range(4)], axis=1).astype(np.float32)
+    prm = RenderParams(step, 1.0, 15.0)
+    target = oracle.forward_image(tgt_vol, dims, tf, prm, cams)
+    dev = dpr.Device(0)
+    if linear:
+        # a tiny volume first, for the camera tables and sums; then each call's next
+        # allocation, its volume scratch, fails
+        _gpu_loss_grad(dpr, dev, vol[:4, :4, :4].copy(), tf, cams, prm, target)
+
+        def fail_next():
+            n, live = C.c_int64(), C.c_int64()
+            dpr.check(dpr.lib.dpr_alloc_stats(C.byref(n), C.byref(live)))
+            monkeypatch.setenv("DPR_FAULT_INJECT", f"alloc:{n.value + 1}")
+        fwd, bwd = dpr.DprRenderFn.forward, dpr.DprRenderFn.backward
+        monkeypatch.setattr(dpr.DprRenderFn, "forward", staticmethod(lambda *a: (fail_next(), fwd(*a))[1]))
+        monkeypatch.setattr(dpr.DprRenderFn, "backward", staticmethod(lambda *a: (fail_next(), bwd(*a))[1]))
+    img, loss, gv, gt = _gpu_loss_grad(dpr, dev, vol, tf, cams, prm, target)
+    L, wv, wt, want = oracle.loss_and_grad(vol, dims, tf, prm, cams, target)
+    err = np.max(np.abs(img - want))
+    rel = [np.linalg.norm(g - w) / np.linalg.norm(w) for g, w in ((gv, wv), (gt, wt))]
+    log(f"{dims} {n_cams} x {size}: image {err:.2e}, volume gradient {rel[0]:.2e}, table gradient {rel[1]:.2e}")
+    assert err <= 2e-5
+    assert max(rel) <= REL_TOL
+    monkeypatch.undo()
+    dev.release()
