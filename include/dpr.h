@@ -254,7 +254,7 @@ void dpr_frame_release(dpr_frame);
  * Segments whose sample point lies in a macrocell of majorant 0 are skipped;
  * they contribute exactly nothing, so skipping never changes a result.
  * The frame must match the camera's size.  The brick's screen tiles go through
- * the persistent kernel of dpr_render_batch (graph-replayed unless
+ * the persistent kernel of dpr_render_batch (graph-replayed like it unless
  * DPR_FLAG_NO_GRAPH); with DPR_FLAG_PLAIN in the render parameters, or with a
  * sample-count buffer attached to `out` (dpr_frame_attach_counts), one plain
  * launch of one thread per pixel renders it instead.  Both give the same bits. */
@@ -297,8 +297,9 @@ dpr_status dpr_render_frame(dpr_world, dpr_frame out);
 
 /* Batched render of n cameras: one persistent launch walks a queue of
  * (camera, brick, screen tile) items, then a tile compositor merges each
- * camera's fragments into outs[c]; replayed from a HIP graph captured on the
- * first call for these frames (flags: DPR_FLAG_PLAIN, DPR_FLAG_NO_GRAPH).
+ * camera's fragments into outs[c]; from the second call in a row for the same
+ * cameras and frames on replayed from a HIP graph (flags: DPR_FLAG_PLAIN,
+ * DPR_FLAG_NO_GRAPH).
  * The results equal dpr_render_frame per camera bit for bit.                   */
 dpr_status dpr_render_batch(dpr_world, const dpr_camera* cams, int32_t n, dpr_frame* outs, uint32_t flags);
 /* Time the candidate tile shapes for this world and camera batch on the GPU and
@@ -325,7 +326,7 @@ dpr_status dpr_set_batch_tile(dpr_world, int32_t tile_w, int32_t tile_h);
  * render (dpr_render_batch with DPR_FLAG_NO_GRAPH, or dpr_render_frame or
  * dpr_render_partial with DPR_FLAG_NO_GRAPH in the render parameters), from HIP
  * events recorded on the device stream around each kernel.  Synchronises.
- * DPR_ERR_INVALID_STATE when the last batched render was a graph replay (or
+ * DPR_ERR_INVALID_STATE when the last batched render was without that flag (or
  * there was none).                                                              */
 dpr_status dpr_batch_timings(dpr_world, float* march_ms, float* composite_ms);
 

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from oracle import RenderParams
-from synth import Camera, fibonacci_cameras, kd_split, make_blobs, make_tf, make_volume_small
+from synth import Camera, even_split, fibonacci_cameras, kd_split, make_blobs, make_tf, make_volume_small
 from tests.gpu_util import TOL_F32, frame_np, log, make_world, oracle_brick
 
 pytestmark = pytest.mark.gpu
@@ -349,3 +349,54 @@ def test_autotune_cache(gpu_lib, dpr, tmp_path, monkeypatch):
         f.release()
     w.release()
     w2.release()
+
+
+@pytest.mark.parametrize("nb, size, tile", [
+    (1, (1040, 700), (8, 8)),     # a group of many sorted lists, one brick
+    (7, (331, 260), (64, 1)),     # tiles that no 4 x 4 patch divides
+    ((7, 5, 2), (150, 131), (16, 8)),    # more groups than the lanes of a wave, more than 16 on a tile
+    ((8, 5, 5), (70, 66), (32, 32)),     # the largest tiles and composites
+])
+def test_moving_camera_queue(gpu_lib, dpr, nb, size, tile):
+    """Frames of a moving camera, enqueued one after the other without a wait and from two
+    streams: the queues built on the device hold every item once and the frames equal the
+    plain launches bit for bit, on their first (direct) and later (graph) renders."""
+    import torch
+    dims, vol, boxes, tf = _scene(nb=nb if isinstance(nb, int) else 1)
+    if not isinstance(nb, int):
+        boxes = even_split(dims, nb)
+    prm = RenderParams(0.5, 0.99, 25.0)
+    cams = [Camera(c.eye, c.center, c.up, 40.0 + 3 * i, *size)
+            for i, c in enumerate(fibonacci_cameras(dims, 8, *size, dist=1.4))]
+    cams.append(Camera((0.45, 0.4, 0.35), (1.5, 1.2, 0.9), (0.0, 0.0, 1.0), 80.0, *size))  # eye inside
+    dev = dpr.Device(0)
+    w = make_world(dpr, dev, vol, dims, boxes, tf, prm, cams[0], mc=8)
+    dpr.check(dpr.lib.dpr_set_batch_tile(w.h, *tile))
+    frames = [dpr.Frame(dev, *size) for _ in cams]
+    w.render_batch(cams, frames, dpr.FLAG_PLAIN)
+    want = [frame_np(f)[:2] for f in frames]
+    assert max(a[..., 3].max() for a, _ in want) > 0.3
+    side = torch.cuda.Stream()
+    for again in range(2):
+        for f in frames:
+            f.rgba.fill_(-1.0)
+            f.depth.fill_(-1.0)
+        torch.cuda.synchronize()
+        for i, (c, f) in enumerate(zip(cams, frames)):
+            if i == 5:
+                dev.set_stream(side)
+            w.set_camera(c)
+            for _ in range(1 + again):
+                w.render_frame(f)
+        torch.cuda.synchronize()
+        for i, (f, (a, z)) in enumerate(zip(frames, want)):
+            got = frame_np(f)[:2]
+            assert np.array_equal(got[0], a) and np.array_equal(got[1], z), (again, i)
+    for i in (0, 8):
+        w.render_batch(cams[i:i + 1], frames[i:i + 1], flags=dpr.FLAG_QUEUE_COVERAGE)
+        items, items_once, slots, slots_once = w.batch_coverage()
+        assert items_once == items > 0 and slots_once == slots == items * tile[0] * tile[1]
+    for f in frames:
+        f.release()
+    w.release()
+    dev.release()
