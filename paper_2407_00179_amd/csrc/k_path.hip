@@ -1,16 +1,15 @@
 // Data-parallel volumetric path tracing with ray forwarding (dpr_render_path).
 //
-// Each brick plays one rank's part.  Rays (camera paths and their shadow rays)
-// live in a pool of 64-byte records and advance in waves: in a wave a ray is
-// worked on until it finishes or until its next tentative collision lies in
-// another brick (it is then handed to that brick for the next wave: the
-// forwarding of rays between ranks); the shadow ray a real collision spawns goes
-// to the next wave while its path goes on.  Records are appended to the
-// next pool with one atomic per wave.  A path's contributions land in fixed
-// slots and are summed in a fixed order, so the image does not depend on the
-// order of rays in the pools, nor on the bricking: the tentative collisions come
-// from majorants on a grid of the whole volume and a counter-based generator
-// keyed by the path.
+// Each brick plays one rank's part: a ray works with the brick that holds its next
+// tentative collision and is forwarded when that is another one.  On one GPU every
+// brick is at hand, so a forwarded ray stays in its lane and only its wave number goes up,
+// as it does for the shadow ray that a real collision spawns; the counters are those of
+// rays handed over between ranks wave by wave.  A launch takes all camera paths to
+// their ends; shadow rays wait in LDS for a free lane of their wave.  A path's contributions
+// land in fixed slots and are summed in a fixed order, so the image does not depend on
+// the order in which rays are taken, nor on the bricking: the tentative collisions come
+// from majorants on a grid of the whole volume and a counter-based generator keyed by
+// the path.
 //
 // Estimator (per path): delta tracking under a piecewise-constant majorant on the
 // global grid of 16^3-cell blocks (D times the TF majorant of the block's value
@@ -21,6 +20,7 @@
 // max_bounces real collisions; leaving the volume box it adds thr * env.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "majorant.h"
@@ -38,16 +38,21 @@ struct PRay {
   uint32_t e;     // path: next event index; shadow: the event that spawned it
   uint32_t meta;  // bit 31 shadow, bit 30 pending, bits 16..23 bounce (path) or slot (shadow),
                   // bits 0..15 shadow step
-  int32_t brick;  // brick that works on the ray in the next wave (-1: none yet)
+  int16_t brick;  // brick that works on the ray (-1: none yet)
+  uint16_t gen;   // wave number
 };
 static_assert(sizeof(PRay) == 64, "ray records are 64 bytes");
 
 constexpr uint32_t kShadowRay = 1u << 31, kPendingEvent = 1u << 30;
 constexpr uint32_t kPathKey1 = 0x243F6A88u;
-constexpr int kStepsPerWave = 1 << 16;  // bound on one ray's steps in one wave
+constexpr int kStepsPerWave = 1 << 16;  // bound on one ray's steps in one wave, and so on a launch's
 constexpr int kMaxWaves = 1 << 14;
 constexpr int kOwnerShift = 4;            // owner and majorant blocks of 16^3 cells
-constexpr int kWavesPerCheck = 4;         // waves enqueued between reads of the pool size
+// counters of a launch, one cache line each: the queues' heads, then the statistics
+// (kStatLines copies, by workgroup), then the output pool's size
+constexpr int kPathQueues = 8, kStatLines = 16, kLineInts = 32;
+constexpr int kCtlInts = (kPathQueues + kStatLines + 1) * kLineInts;
+constexpr uint32_t kSeesEnv = 1u << 16, kMissed = 1u << 17;
 
 struct PathG {
   const BrickG* bricks;
@@ -66,12 +71,15 @@ struct PathG {
   uint32_t seed;
   int vacuum;       // sbar == 0: nothing can collide, every path sees the environment
   float4* contrib;  // B + 1 slots per path: NEE at real collisions 0..B-1, environment at B
-  PRay* out;
-  int* out_count;
-  int* cursor_in;   // records of the input pool taken so far (this wave)
-  int* cursor_out;  // the same for the output pool: cleared for the next wave
+  // per path: its real collisions (slots 0.. of contrib are written), kSeesEnv: slot B is,
+  // kMissed: nothing is, the path sees the environment
+  uint32_t* ends;
+  PRay* out;        // rays left over for another launch
   int out_cap;
-  unsigned long long* stats;  // events, shadow steps, forwards, pool overflows, waves with rays
+  int* ctl;         // kCtlInts counters
+};
+struct PathStatsG {
+  unsigned long long events, shadow_steps, forwards, waves, stuck;
 };
 
 // Philox4x32-10 (Salmon et al., SC 2011): ten rounds of two 32x32->64 products,
@@ -158,24 +166,34 @@ __device__ __forceinline__ bool flight(const SceneG& sc, const PathG& pg, const 
   const float t_box = exit_dist(pg, x, w);
   float t = 0.f, acc = 0.f;
   const int max_steps = 2 * (pg.odim[0] + pg.odim[1] + pg.odim[2]) + 8;
-  for (int it = 0; it < max_steps; ++it) {
-    const float tn = fminf(tmax[0], fminf(tmax[1], tmax[2]));
-    const float se = fminf(tn, t_box);
-    const float sb = pg.sgrid[(b[2] * pg.odim[1] + b[1]) * pg.odim[0] + b[0]];
-    const float gain = sb * (se - t);
-    if (acc + gain >= target) {
-      t_hit = t + (target - acc) / sb;
-      return true;
-    }
-    acc += gain;
-    t = se;
-    if (!(se < t_box)) return false;
+  // the blocks' majorants are requested kAhead at a time: the walk itself does not depend on them
+  constexpr int kAhead = 4;
+  for (int it = 0; it < max_steps; it += kAhead) {
+    float se[kAhead], sb[kAhead];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      if (tmax[a] == tn) {
-        b[a] = min(max(b[a] + step[a], 0), pg.odim[a] - 1);
-        tmax[a] += tdel[a];
+    for (int j = 0; j < kAhead; ++j) {
+      const float tn = fminf(tmax[0], fminf(tmax[1], tmax[2]));
+      se[j] = fminf(tn, t_box);
+      sb[j] = ld_global(pg.sgrid, (uint32_t)((b[2] * pg.odim[1] + b[1]) * pg.odim[0] + b[0]));
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        if (tmax[a] == tn) {
+          b[a] = min(max(b[a] + step[a], 0), pg.odim[a] - 1);
+          tmax[a] += tdel[a];
+        }
       }
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (it + j == max_steps) return false;
+      const float gain = sb[j] * (se[j] - t);
+      if (acc + gain >= target) {
+        t_hit = t + (target - acc) / sb[j];
+        return true;
+      }
+      acc += gain;
+      t = se[j];
+      if (!(se[j] < t_box)) return false;
     }
   }
   return false;
@@ -207,232 +225,305 @@ __device__ __forceinline__ void add_contrib(const PathG& pg, uint32_t pid, int s
   pg.contrib[(size_t)pid * (pg.B + 1) + slot] = make_float4(r, g, b, 0.f);
 }
 
-// Append up to two records per lane with one atomic per wave (called by every
-// lane of the wave at the same point).
-__device__ __forceinline__ void emit2(const PathG& pg, const PRay& ra, bool ha, const PRay& rb, bool hb) {
+// Append a record per lane with one atomic per wave (called by every lane of the wave at
+// the same point).
+__device__ __forceinline__ void emit(const PathG& pg, const PRay& r, bool has) {
   const int lane = threadIdx.x & 63;
-  const uint64_t ma = __ballot(ha), mb = __ballot(hb);
-  const int na = __popcll(ma), total = na + __popcll(mb);
-  if (total == 0) return;
+  const uint64_t m = __ballot(has);
+  if (m == 0) return;
   int base = 0;
-  if (lane == 0) base = atomicAdd(pg.out_count, total);
+  if (lane == 0) base = atomicAdd(pg.ctl + (kPathQueues + kStatLines) * kLineInts, __popcll(m));
   base = __shfl(base, 0);
-  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const int ia = base + __popcll(ma & lt), ib = base + na + __popcll(mb & lt);
-  bool over = false;
-  if (ha) {
-    if (ia < pg.out_cap) pg.out[ia] = ra;
-    else over = true;
-  }
-  if (hb) {
-    if (ib < pg.out_cap) pg.out[ib] = rb;
-    else over = true;
-  }
-  if (over) atomicAdd(pg.stats + 3, 1ull);
+  const int i = base + __popcll(m & ~(~0ull << lane));
+  if (has && i < pg.out_cap) pg.out[i] = r;
 }
 
-__device__ __forceinline__ void wave_stats(const PathG& pg, unsigned ev, unsigned st, unsigned fw) {
+__device__ __forceinline__ PathStatsG* stats_line(const PathG& pg) {
+  return (PathStatsG*)(pg.ctl + (kPathQueues + (blockIdx.x & (kStatLines - 1))) * kLineInts);
+}
+
+__device__ __forceinline__ void wave_stats(const PathG& pg, unsigned ev, unsigned st, unsigned fw, unsigned waves) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     ev += __shfl_xor(ev, o);
     st += __shfl_xor(st, o);
     fw += __shfl_xor(fw, o);
+    waves = max(waves, __shfl_xor(waves, o));
   }
   if ((threadIdx.x & 63) == 0) {
-    if (ev) atomicAdd(pg.stats + 0, (unsigned long long)ev);
-    if (st) atomicAdd(pg.stats + 1, (unsigned long long)st);
-    if (fw) atomicAdd(pg.stats + 2, (unsigned long long)fw);
+    PathStatsG* s = stats_line(pg);
+    if (ev) atomicAdd(&s->events, (unsigned long long)ev);
+    if (st) atomicAdd(&s->shadow_steps, (unsigned long long)st);
+    if (fw) atomicAdd(&s->forwards, (unsigned long long)fw);
+    if (waves) atomicMax(&s->waves, (unsigned long long)waves);
   }
 }
 
-// Camera paths: one per (pixel, sample), started at the volume box entry with no
-// brick.  The first flight needs only the majorant grid, which every rank holds,
-// so the brick of the first tentative collision starts the path without a
-// hand-over.
-__global__ __launch_bounds__(256) void path_init_kernel(PathG pg, CamG cam, int W, int H) {
-  const long long total = (long long)W * H * pg.spp;
-  const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-  PRay r{};
-  bool live = false;
-  if (id < total) {
-    const uint32_t pid = (uint32_t)id;
-    const int pix = (int)(id / pg.spp);
-    double d[3];
-    camera_ray(cam, pix % W, pix / W, d);
-    const double lo[3] = {0.0, 0.0, 0.0}, hi[3] = {pg.box[0], pg.box[1], pg.box[2]};
-    double t_in, t_out;
-    if (!pg.vacuum && clip_box(cam.eye, d, lo, hi, t_in, t_out)) {
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        r.x[a] = (float)(cam.eye[a] + t_in * d[a]);
-        r.w[a] = (float)d[a];
-        r.t[a] = 1.f;
-      }
-      r.pid = pid;
-      r.brick = -1;
-      live = true;
-    } else {
-      add_contrib(pg, pid, pg.B, pg.Le[0], pg.Le[1], pg.Le[2]);
-    }
-  }
-  const PRay none{};
-  emit2(pg, r, live, none, false);
+__global__ void path_reset_kernel(int* ctl, int n) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) ctl[i] = 0;
 }
 
-// n_in: device count of the input pool (written by the previous wave).  A resident
-// grid takes its records through pg.cursor_in; the loop runs while any lane of the
-// wave holds a ray, so the refills and appends stay convergent.
+// The shadow rays of a wave that wait for a lane: what differs from ray to ray, a word of
+// each side by side (no bank conflicts).  What does not fit goes to the output pool.
+constexpr int kShadowQueue = 256;
+struct ShadowQueue {
+  float x[3][kShadowQueue], t[3][kShadowQueue];
+  uint32_t pid[kShadowQueue], e[kShadowQueue], meta[kShadowQueue], brick_gen[kShadowQueue];
+};
+
+// All rays of a launch: the camera paths (in null) in blocks of 64, or the records that an
+// earlier launch left over.  A resident grid takes blocks from the queue of its workgroups'
+// XCD.  A lane holds one ray and does one tentative collision at a time; it keeps a camera
+// path across real collisions and a ray that changes bricks; free lanes take shadow rays of
+// their wave first, then new rays, 16 or more at a time.  The first flight of a path needs
+// only the majorant grid, which every rank holds, so the brick of the first tentative
+// collision starts it without a hand-over.
+//
+// A launch per wave with rays handed over through a pool in memory, and the host reading its
+// size every four, took 2170 us for 1024^2 paths of up to 4 bounces in 2 x 2 x 2 bricks of a
+// 512^3 volume (0.8 M tentative collisions in 12 launches of 38 to 277 us); one launch 290.
+// It is bound by the latency of its longest chains (a flight's block majorants, then eight
+// voxels, per tentative collision), so a wave's paths come from all over the image: 16
+// pieces of 2 x 2 pixels per block (tiles of 8 x 8 pixels 515 us, four pieces of 4 x 4 335,
+// single pixels 302); bricks' descriptors in LDS gain 2%, a fourth wave per SIMD nothing.
+// With room for 256 shadow rays none is left over with up to 4 bounces (128: a second
+// launch, 663 us).
 template <typename T, bool WIDE>
-__global__ __launch_bounds__(256) void path_trace_kernel(SceneG sc, PathG pg, const float4* __restrict__ tf,
-                                                         const PRay* __restrict__ in,
-                                                         const int* __restrict__ n_in_dev) {
+__global__ __launch_bounds__(256) void path_trace_kernel(SceneG sc, PathG pg, CamG cam, const float4* __restrict__ tf,
+                                                         const PRay* __restrict__ in, int n_in) {
   extern __shared__ float4 tf_lds[];
+  __shared__ ShadowQueue queues[4];
   float4* tfb = tf_lds;
   float4* tfs = tf_lds + sc.ntf;
   stage_tf(tf, sc.ntf, tfb, tfs, threadIdx.x, 256);
   __syncthreads();
-  const int n_in = min(*n_in_dev, pg.out_cap);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (n_in > 0) atomicAdd(pg.stats + 4, 1ull);
-    *pg.cursor_out = 0;
-  }
   const int lane = threadIdx.x & 63;
-  const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
-  unsigned ev = 0, st = 0, fw = 0;
-  // Each lane holds one ray.  Idle lanes take the next records of the input pool
-  // (one atomic per wave); a camera path stays in its lane across real collisions
-  // (its shadow ray goes to the next wave), so the wave's long chains overlap.
+  const uint64_t lt_mask = ~(~0ull << lane);
+  ShadowQueue& sq = queues[threadIdx.x >> 6];
+  int n_sq = 0;
+  // blocks of 64 rays: of the queue, every kPathQueues-th one; a wave's first is its own
+  const int tiles_x = (cam.W + 1) >> 1, n_tiles = tiles_x * ((cam.H + 1) >> 1) * pg.spp;
+  const int n_blocks = in ? (n_in + 63) >> 6 : (n_tiles + 15) >> 4;
+  const int slot = blockIdx.x & (kPathQueues - 1), own = gridDim.x / kPathQueues * 4;
+  int next = (int)(threadIdx.x >> 6) * (gridDim.x / kPathQueues) + blockIdx.x / kPathQueues;
+  int block = 0, block_next = 64;
+  bool exhausted = false;
+
+  unsigned ev = 0, st = 0, fw = 0, waves = 0;
   PRay r{};
-  bool have = false, exhausted = false;
+  int brick = -1, gen = 0, steps = 0;
+  bool have = false;
   for (;;) {
-    const uint64_t idle = __ballot(!have);
-    if (idle && !exhausted) {
-      int base = 0;
-      if (lane == 0) base = atomicAdd(pg.cursor_in, __popcll(idle));
-      base = __shfl(base, 0);
-      if (base + __popcll(idle) >= n_in) exhausted = true;
-      if (!have) {
-        const int i = base + __popcll(idle & lt_mask);
-        if (i < n_in) {
-          r = in[i];
-          have = true;
-        }
-      }
-    }
-    if (__ballot(have) == 0) break;
-  PRay ra{}, rb{};
-  bool ha = false, hb = false;
-  if (have) {
-    have = false;
-    if (r.meta & kShadowRay) {
-      const int slot = (int)((r.meta >> 16) & 0xff);
-      for (int it = 0;; ++it) {
-        if (it == kStepsPerWave) {  // keep it for the next wave
-          ra = r;
-          ha = true;
-          break;
-        }
-        if (!(r.meta & kPendingEvent)) {
-          const uint4 q = philox(r.pid, r.e, 1u, r.meta & 0xffffu, pg.seed, kPathKey1);
-          float s;
-          ++st;
-          if (!flight(sc, pg, r.x, r.w, -logf(u01(q.x)), s)) {
-            add_contrib(pg, r.pid, slot, r.t[0] * r.a, r.t[1] * r.a, r.t[2] * r.a);
-            break;
-          }
+    uint64_t idle = __ballot(!have);
+    if (idle && n_sq) {
+      const int n = min(__popcll(idle), n_sq), i = n_sq - n + __popcll(idle & lt_mask);
+      if (!have && i < n_sq) {
 #pragma unroll
-          for (int a = 0; a < 3; ++a) r.x[a] = fmaf(s, r.w[a], r.x[a]);
-          r.meta |= kPendingEvent;
+        for (int a = 0; a < 3; ++a) {
+          r.x[a] = sq.x[a][i];
+          r.t[a] = sq.t[a][i];
+          r.w[a] = pg.l[a];
         }
-        const int owner = locate(sc, pg, r.x, r.brick);
-        if (owner >= 0 && owner != r.brick) {
-          r.brick = owner;
-          ra = r;
-          ha = true;
-          ++fw;
-          break;
-        }
-        float sigma = 0.f, alb[3];
-        if (owner >= 0) medium<T, WIDE>(sc, pg.bricks[owner], tfb, tfs, r.x, sigma, alb);
-        const float sbq = sbar_at(sc, pg, r.x);
-        if (sbq > 0.f) r.a *= 1.f - sigma / sbq;
-        r.meta = (r.meta & ~(kPendingEvent | 0xffffu)) | (((r.meta & 0xffffu) + 1u) & 0xffffu);
-        if (r.a == 0.f) break;  // nothing more can reach the light (the slot stays 0)
+        r.a = 1.f;
+        r.pid = sq.pid[i];
+        r.e = sq.e[i];
+        r.meta = sq.meta[i];
+        brick = (int16_t)(sq.brick_gen[i] & 0xffffu);
+        gen = (int)(sq.brick_gen[i] >> 16);
+        waves = max(waves, (unsigned)gen + 1u);
+        steps = 0;
+        have = true;
       }
-    } else {
-      for (int it = 0;; ++it) {
-        if (it == kStepsPerWave) {
-          ra = r;
-          ha = true;
+      n_sq -= n;
+      idle = __ballot(!have);
+    }
+    while (!exhausted && __popcll(idle) >= 16) {
+      if (block_next == 64) {
+        int n = next;
+        if (n < 0) {
+          if (lane == 0) n = atomicAdd(pg.ctl + slot * kLineInts, 1) + own;
+          n = __builtin_amdgcn_readfirstlane(n);
+        }
+        next = -1;
+        block = n * kPathQueues + slot;
+        if (n >= (n_blocks - slot + kPathQueues - 1) / kPathQueues) {
+          exhausted = true;
           break;
         }
-        if (!(r.meta & kPendingEvent)) {
-          const uint4 q = philox(r.pid, r.e, 0u, 0u, pg.seed, kPathKey1);
-          float t;
-          if (!flight(sc, pg, r.x, r.w, -logf(u01(q.x)), t)) {  // leaves the volume
-            add_contrib(pg, r.pid, pg.B, r.t[0] * pg.Le[0], r.t[1] * pg.Le[1], r.t[2] * pg.Le[2]);
-            break;
+        block_next = 0;
+      }
+      const int i = block_next + __popcll(idle & lt_mask);
+      block_next = min(block_next + __popcll(idle), 64);
+      if (!have && i < 64) {
+        if (in) {
+          if ((long long)block * 64 + i < n_in) {
+            r = in[(size_t)block * 64 + i];
+            brick = r.brick;
+            gen = r.gen;
+            have = true;
           }
+        } else {
+          const int part = block + (i >> 2) * n_blocks, tile = part / pg.spp;
+          const int px = tile % tiles_x * 2 + (i & 1), py = tile / tiles_x * 2 + ((i >> 1) & 1);
+          if (part < n_tiles && px < cam.W && py < cam.H) {
+            const uint32_t pid = (uint32_t)(((size_t)py * cam.W + px) * pg.spp + part % pg.spp);
+            double d[3];
+            camera_ray(cam, px, py, d);
+            const double lo[3] = {0.0, 0.0, 0.0}, hi[3] = {pg.box[0], pg.box[1], pg.box[2]};
+            double t_in, t_out;
+            if (!pg.vacuum && clip_box(cam.eye, d, lo, hi, t_in, t_out)) {
+#pragma unroll
+              for (int a = 0; a < 3; ++a) {
+                r.x[a] = (float)(cam.eye[a] + t_in * d[a]);
+                r.w[a] = (float)d[a];
+                r.t[a] = 1.f;
+              }
+              r.pid = pid;
+              r.e = 0;
+              r.meta = 0;
+              brick = -1;
+              gen = 0;
+              have = true;
+            } else {
+              pg.ends[pid] = kMissed;
+            }
+          }
+        }
+        if (have) {
+          waves = max(waves, (unsigned)gen + 1u);
+          steps = 0;
+        }
+      }
+      idle = __ballot(!have);
+    }
+    if (idle == ~0ull) break;
+
+    // ---- one tentative collision
+    bool spawn = false, keep = false;
+    uint32_t spawn_e = 0, spawn_meta = 0;
+    if (have) {
+      const bool shadow = (r.meta & kShadowRay) != 0;
+      const int k = (int)((r.meta >> 16) & 0xff);  // real collisions so far (path), slot (shadow)
+      if (steps == kStepsPerWave) {
+        keep = true;
+        have = false;
+      } else if (!(r.meta & kPendingEvent)) {
+        const uint4 q = philox(r.pid, r.e, shadow ? 1u : 0u, shadow ? r.meta & 0xffffu : 0u, pg.seed, kPathKey1);
+        if (shadow) ++st;
+        float t;
+        if (!flight(sc, pg, r.x, r.w, -logf(u01(q.x)), t)) {  // leaves the volume
+          if (shadow) {
+            add_contrib(pg, r.pid, k, r.t[0] * r.a, r.t[1] * r.a, r.t[2] * r.a);
+          } else {
+            add_contrib(pg, r.pid, pg.B, r.t[0] * pg.Le[0], r.t[1] * pg.Le[1], r.t[2] * pg.Le[2]);
+            pg.ends[r.pid] = kSeesEnv | (uint32_t)k;
+          }
+          have = false;
+        } else {
 #pragma unroll
           for (int a = 0; a < 3; ++a) r.x[a] = fmaf(t, r.w[a], r.x[a]);
-          r.a = u01(q.y);
-          r.b = u01(q.z);
-          r.c = u01(q.w);
+          if (!shadow) {
+            r.a = u01(q.y);
+            r.b = u01(q.z);
+            r.c = u01(q.w);
+          }
           r.meta |= kPendingEvent;
         }
-        const int owner = locate(sc, pg, r.x, r.brick);
-        if (owner >= 0 && owner != r.brick) {
-          if (r.brick >= 0) {
-            r.brick = owner;
-            ra = r;
-            ha = true;
+      }
+      if (have) {
+        ++steps;
+        const int owner = locate(sc, pg, r.x, brick);
+        if (owner >= 0 && owner != brick) {
+          if (brick >= 0) {
             ++fw;
-            break;
+            ++gen;
+            waves = max(waves, (unsigned)gen + 1u);
+            steps = 1;
           }
-          r.brick = owner;  // a camera path starts with the brick of its first tentative collision
+          brick = owner;
         }
-        ++ev;
         float sigma = 0.f, alb[3] = {0.f, 0.f, 0.f};
         if (owner >= 0) medium<T, WIDE>(sc, pg.bricks[owner], tfb, tfs, r.x, sigma, alb);
         r.meta &= ~kPendingEvent;
-        const uint32_t e = r.e++;
         const float sbq = sbar_at(sc, pg, r.x);
-        if (sbq > 0.f && r.a < sigma / sbq) {  // real collision
-          const int k = (int)((r.meta >> 16) & 0xff);
-#pragma unroll
-          for (int a = 0; a < 3; ++a) r.t[a] *= alb[a];
-          PRay s{};
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            s.x[a] = r.x[a];
-            s.w[a] = pg.l[a];
-            s.t[a] = r.t[a] * pg.Ll[a];
+        if (shadow) {
+          if (sbq > 0.f) r.a *= 1.f - sigma / sbq;
+          r.meta = (r.meta & ~0xffffu) | (((r.meta & 0xffffu) + 1u) & 0xffffu);
+          if (r.a == 0.f) {  // nothing more can reach the light
+            add_contrib(pg, r.pid, k, 0.f, 0.f, 0.f);
+            have = false;
           }
-          s.a = 1.f;
-          s.pid = r.pid;
-          s.e = e;
-          s.meta = kShadowRay | ((uint32_t)k << 16);
-          s.brick = owner;
-          rb = s;
-          hb = true;
-          if (k + 1 >= pg.B) break;  // the path ends at its last real collision
-          r.meta = (r.meta & ~(0xffu << 16)) | ((uint32_t)(k + 1) << 16);
-          const float z = 1.f - 2.f * r.b;
-          const float rr = sqrtf(fmaxf(0.f, 1.f - z * z));
-          float sp, cp;
-          sincosf(6.28318530717958647692f * r.c, &sp, &cp);
-          r.w[0] = rr * cp;
-          r.w[1] = rr * sp;
-          r.w[2] = z;
-          have = true;  // the path goes on in this lane
-          break;
+        } else {
+          ++ev;
+          spawn_e = r.e++;
+          if (sbq > 0.f && r.a < sigma / sbq) {  // real collision
+#pragma unroll
+            for (int a = 0; a < 3; ++a) r.t[a] *= alb[a];
+            spawn_meta = kShadowRay | ((uint32_t)k << 16);
+            spawn = true;
+            steps = 0;
+            if (k + 1 >= pg.B) {  // the path ends at its last real collision
+              pg.ends[r.pid] = (uint32_t)(k + 1);
+              have = false;
+            } else {
+              r.meta = (r.meta & ~(0xffu << 16)) | ((uint32_t)(k + 1) << 16);
+              const float z = 1.f - 2.f * r.b;
+              const float rr = sqrtf(fmaxf(0.f, 1.f - z * z));
+              float sp, cp;
+              sincosf(6.28318530717958647692f * r.c, &sp, &cp);
+              r.w[0] = rr * cp;
+              r.w[1] = rr * sp;
+              r.w[2] = z;
+            }
+          }
         }
       }
     }
+
+    // ---- shadow rays to the wave's queue; what it cannot hold, and rays of too many
+    // steps, to the output pool, one wave on
+    const uint64_t spawned = __ballot(spawn);
+    const int qi = n_sq + __popcll(spawned & lt_mask);
+    if (spawn && qi < kShadowQueue) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        sq.x[a][qi] = r.x[a];
+        sq.t[a][qi] = r.t[a] * pg.Ll[a];
+      }
+      sq.pid[qi] = r.pid;
+      sq.e[qi] = spawn_e;
+      sq.meta[qi] = spawn_meta;
+      sq.brick_gen[qi] = ((uint32_t)brick & 0xffffu) | ((uint32_t)(gen + 1) << 16);
+    }
+    n_sq = min(n_sq + __popcll(spawned), kShadowQueue);
+    const bool spill = spawn && qi >= kShadowQueue;
+    if (__ballot(spill || keep)) {
+      PRay o = r;
+      if (spill) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          o.w[a] = pg.l[a];
+          o.t[a] = r.t[a] * pg.Ll[a];
+        }
+        o.a = 1.f;
+        o.e = spawn_e;
+        o.meta = spawn_meta;
+      }
+      o.brick = (int16_t)brick;
+      o.gen = (uint16_t)(gen + 1);
+      emit(pg, o, spill || keep);
+    }
+    // (the wave's own LDS operations complete in order; the compiler keeps it too)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // a ray of too many waves ends, and the call fails
+    if (gen >= kMaxWaves - 2) {
+      if (have) atomicAdd(&stats_line(pg)->stuck, 1ull);
+      have = false;
+      gen = 0;
+    }
   }
-  emit2(pg, ra, ha, rb, hb);
-  }
-  wave_stats(pg, ev, st, fw);
+  wave_stats(pg, ev, st, fw, waves);
 }
 
 // Pixel radiance: the contributions of its paths, summed in slot order, then
@@ -443,13 +534,23 @@ __global__ __launch_bounds__(256) void path_resolve_kernel(PathG pg, int n_pixel
   if (p >= n_pixels) return;
   float sr = 0.f, sg = 0.f, sb = 0.f;
   for (int s = 0; s < pg.spp; ++s) {
-    const float4* c = pg.contrib + ((size_t)p * pg.spp + s) * (pg.B + 1);
+    const size_t path = (size_t)p * pg.spp + s;
+    const float4* c = pg.contrib + path * (pg.B + 1);
+    const uint32_t end = pg.ends[path];
     float lr = 0.f, lg = 0.f, lb = 0.f;
-    for (int k = 0; k <= pg.B; ++k) {
-      const float4 v = c[k];
-      lr += v.x;
-      lg += v.y;
-      lb += v.z;
+    if (end & kMissed) {
+      lr = pg.Le[0];
+      lg = pg.Le[1];
+      lb = pg.Le[2];
+    } else {
+      const int n = min((int)(end & 0xffffu), pg.B);
+      for (int k = 0; k <= n; ++k) {  // (the other slots hold nothing)
+        if (k == n && !(end & kSeesEnv)) break;
+        const float4 v = c[k < n ? k : pg.B];
+        lr += v.x;
+        lg += v.y;
+        lb += v.z;
+      }
     }
     sr += lr;
     sg += lg;
@@ -551,10 +652,11 @@ __global__ __launch_bounds__(256) void block_majorant_kernel(const uint32_t* __r
 struct PathState {
   PRay* pool[2] = {nullptr, nullptr};
   size_t cap = 0;  // records per pool
-  float4* contrib = nullptr;
+  float4* contrib = nullptr;  // and behind it the paths' ends
   size_t contrib_cap = 0;
   BrickG* d_bricks = nullptr;
   int brick_cap = 0;
+  std::vector<BrickG> h_bricks;  // what d_bricks holds
   int16_t* d_owner = nullptr;
   size_t owner_cap = 0;
   uint32_t* d_lo = nullptr;  // encoded block ranges
@@ -565,9 +667,8 @@ struct PathState {
   size_t grid_n = 0;
   uint64_t owner_version = 0;
   int odim[3] = {0, 0, 0};
-  int* d_count = nullptr;  // [0], [1]: sizes of the two pools
-  unsigned long long* d_stats = nullptr;
-  int* h_count = nullptr;  // pinned
+  int* d_ctl = nullptr;
+  int* h_ctl = nullptr;  // pinned
 };
 
 void path_state_free(PathState* p) {
@@ -580,18 +681,13 @@ void path_state_free(PathState* p) {
   dev_free(p->d_lo);
   dev_free(p->d_hi);
   dev_free(p->d_sgrid);
-  dev_free(p->d_count);
-  dev_free(p->d_stats);
-  host_free(p->h_count);
+  dev_free(p->d_ctl);
+  host_free(p->h_ctl);
   delete p;
 }
 
 template <typename T, bool WIDE>
-static void launch_trace(const SceneG& sc, const PathG& pg, const float4* tf, const PRay* in, const int* n,
-                         int grid, size_t lds, hipStream_t st) {
-  // (pg.cursor_in counts the records of `in` taken; pg.cursor_out is cleared by the kernel)
-  hipLaunchKernelGGL((path_trace_kernel<T, WIDE>), dim3((unsigned)grid), dim3(256), lds, st, sc, pg, tf, in, n);
-}
+static const void* trace_fn() { return (const void*)path_trace_kernel<T, WIDE>; }
 
 }  // namespace dpr
 
@@ -641,26 +737,27 @@ extern "C" dpr_status dpr_render_path(dpr_world w, const dpr_path_params* prm, d
     if ((s = dev_alloc((void**)&ps->pool[1], (size_t)slots * sizeof(PRay), "path ray pool")) != DPR_OK) return s;
     ps->cap = (size_t)slots;
   }
-  if ((size_t)slots > ps->contrib_cap) {
+  const size_t contrib_bytes = (size_t)slots * sizeof(float4) + (size_t)n_paths * sizeof(uint32_t);
+  if (contrib_bytes > ps->contrib_cap) {
     DPR_HIP(hipStreamSynchronize(st));
     dev_free(ps->contrib);
     ps->contrib = nullptr;
     ps->contrib_cap = 0;
-    if ((s = dev_alloc((void**)&ps->contrib, (size_t)slots * sizeof(float4), "path contributions")) != DPR_OK)
-      return s;
-    ps->contrib_cap = (size_t)slots;
+    if ((s = dev_alloc((void**)&ps->contrib, contrib_bytes, "path contributions")) != DPR_OK) return s;
+    ps->contrib_cap = contrib_bytes;
   }
   if (K > ps->brick_cap) {
     DPR_HIP(hipStreamSynchronize(st));
     dev_free(ps->d_bricks);
     ps->d_bricks = nullptr;
+    ps->brick_cap = 0;
+    ps->h_bricks.clear();
     if ((s = dev_alloc((void**)&ps->d_bricks, (size_t)K * sizeof(BrickG), "path bricks")) != DPR_OK) return s;
     ps->brick_cap = K;
   }
-  if (!ps->d_count) {
-    if ((s = dev_alloc((void**)&ps->d_count, 4 * sizeof(int), "path pool sizes and cursors")) != DPR_OK) return s;
-    if ((s = dev_alloc((void**)&ps->d_stats, 5 * sizeof(unsigned long long), "path stats")) != DPR_OK) return s;
-    if ((s = host_alloc((void**)&ps->h_count, 2 * sizeof(int), "path pool sizes (host)")) != DPR_OK) return s;
+  if (!ps->h_ctl) {
+    if (!ps->d_ctl && (s = dev_alloc((void**)&ps->d_ctl, kCtlInts * sizeof(int), "path counters")) != DPR_OK) return s;
+    if ((s = host_alloc((void**)&ps->h_ctl, kCtlInts * sizeof(int), "path counters (host)")) != DPR_OK) return s;
   }
   // owner table of 16^3-cell blocks, rebuilt when bricks were added
   int od[3];
@@ -711,18 +808,18 @@ extern "C" dpr_status dpr_render_path(dpr_world w, const dpr_path_params* prm, d
     views[i] = w->bricks[i].device_view(false, w->params.flags & DPR_FLAG_WIDE_OFFSETS);
     wide |= views[i].wide;
   }
-  // the views are staged through pageable memory: wait for the copy before they change
-  DPR_HIP(hipMemcpyAsync(ps->d_bricks, views.data(), (size_t)K * sizeof(BrickG), hipMemcpyHostToDevice, st));
+  if (ps->h_bricks.size() != views.size() || memcmp(ps->h_bricks.data(), views.data(), K * sizeof(BrickG)) != 0) {
+    // (staged through pageable memory: wait for the copy)
+    ps->h_bricks.clear();
+    DPR_HIP(hipMemcpyAsync(ps->d_bricks, views.data(), (size_t)K * sizeof(BrickG), hipMemcpyHostToDevice, st));
+    DPR_HIP(hipStreamSynchronize(st));
+    ps->h_bricks = views;
+  }
 
   const SceneG sc = make_scene(w);
+  // the majorant: D times the largest TF opacity
   float amax = 0.f;
-  // the majorant: D times the largest TF opacity (the TF is staged on the host)
-  {
-    std::vector<float4> tfh(w->ntf);
-    DPR_HIP(hipMemcpyAsync(tfh.data(), w->tf_dev, (size_t)w->ntf * sizeof(float4), hipMemcpyDeviceToHost, st));
-    DPR_HIP(hipStreamSynchronize(st));
-    for (const auto& v : tfh) amax = std::max(amax, v.w);
-  }
+  for (int i = 0; i < w->ntf; ++i) amax = std::max(amax, w->tf_host[i].w);
   // majorant grid, rebuilt after a commit or a TF change
   if (ps->grid_commit != w->commit_version || ps->grid_tf != w->tf_version || ps->grid_n != n_own) {
     if (n_own > ps->grid_cap) {
@@ -797,71 +894,60 @@ extern "C" dpr_status dpr_render_path(dpr_world w, const dpr_path_params* prm, d
   pg.spp = prm->spp;
   pg.seed = prm->seed;
   pg.contrib = ps->contrib;
-  pg.out_count = ps->d_count;
+  pg.ends = (uint32_t*)(ps->contrib + slots);
   pg.out_cap = (int)ps->cap;
-  pg.stats = ps->d_stats;
-  DPR_HIP(hipMemsetAsync(ps->contrib, 0, (size_t)slots * sizeof(float4), st));
-  DPR_HIP(hipMemsetAsync(ps->d_count, 0, 4 * sizeof(int), st));
-  DPR_HIP(hipMemsetAsync(ps->d_stats, 0, 5 * sizeof(unsigned long long), st));
-
-  int cur = 0;
-  pg.out = ps->pool[cur];
+  pg.ctl = ps->d_ctl;
   pg.vacuum = !(pg.sbar > 0.f);
-  const CamG cam = make_cam(w->cam);
-  hipLaunchKernelGGL(path_init_kernel, dim3((unsigned)((n_paths + 255) / 256)), dim3(256), 0, st, pg, cam, out->w,
-                     out->h);
-  DPR_HIP(hipGetLastError());
-  DPR_HIP(hipMemcpyAsync(ps->h_count, ps->d_count, sizeof(int), hipMemcpyDeviceToHost, st));
-  DPR_HIP(hipStreamSynchronize(st));
-  int n = ps->h_count[0];
+  CamG cam = make_cam(w->cam);
   const size_t lds = 2 * sizeof(float4) * (size_t)sc.ntf;
   const bool f16 = K > 0 && w->bricks[0].dtype == DPR_F16;
-  // a resident grid walks whatever the previous wave left; the host reads the pool
-  // size only every kWavesPerCheck waves (later waves of a batch may find it empty)
-  const void* fn = f16 ? (wide ? (const void*)path_trace_kernel<__half, true> : (const void*)path_trace_kernel<__half, false>)
-                       : (wide ? (const void*)path_trace_kernel<float, true> : (const void*)path_trace_kernel<float, false>);
+  const void* fn = f16 ? (wide ? trace_fn<__half, true>() : trace_fn<__half, false>())
+                       : (wide ? trace_fn<float, true>() : trace_fn<float, false>());
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-  const int grid = w->dev->cu_count * per_cu;
-  int enqueued = 0;
-  while (n > 0) {
-    for (int j = 0; j < kWavesPerCheck; ++j) {
-      if (++enqueued > kMaxWaves) return fail(DPR_ERR_DEVICE, "dpr_render_path: more than %d waves", kMaxWaves);
-      const PRay* in = ps->pool[cur];
-      const int* n_in = ps->d_count + cur;
-      cur ^= 1;
-      pg.cursor_in = ps->d_count + 2 + (cur ^ 1);
-      pg.out = ps->pool[cur];
-      pg.out_count = ps->d_count + cur;
-      pg.cursor_out = ps->d_count + 2 + cur;
-      DPR_HIP(hipMemsetAsync(pg.out_count, 0, sizeof(int), st));
-      if (f16)
-        wide ? launch_trace<__half, true>(sc, pg, w->tf_dev, in, n_in, grid, lds, st)
-             : launch_trace<__half, false>(sc, pg, w->tf_dev, in, n_in, grid, lds, st);
-      else
-        wide ? launch_trace<float, true>(sc, pg, w->tf_dev, in, n_in, grid, lds, st)
-             : launch_trace<float, false>(sc, pg, w->tf_dev, in, n_in, grid, lds, st);
-      DPR_HIP(hipGetLastError());
-    }
-    DPR_HIP(hipMemcpyAsync(ps->h_count, ps->d_count + cur, sizeof(int), hipMemcpyDeviceToHost, st));
+  const int grid = std::max(kPathQueues, w->dev->cu_count * per_cu / kPathQueues * kPathQueues);
+  const float4* tf = w->tf_dev;
+  const PRay* in = nullptr;
+  int n_in = 0, cur = 0;
+  hipLaunchKernelGGL(path_reset_kernel, dim3(1), dim3(256), 0, st, ps->d_ctl, kCtlInts);
+  PathStatsG total{};
+  for (;;) {
+    pg.out = ps->pool[cur];
+    void* args[] = {(void*)&sc, (void*)&pg, (void*)&cam, (void*)&tf, (void*)&in, (void*)&n_in};
+    DPR_HIP(hipLaunchKernel(fn, dim3((unsigned)grid), dim3(256), args, lds, st));
+    // (not the image yet where rays are left over, but mostly none are)
+    const int P = out->w * out->h;
+    hipLaunchKernelGGL(path_resolve_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, pg, P,
+                       (float4*)out->rgba, out->depth);
+    DPR_HIP(hipGetLastError());
+    DPR_HIP(hipMemcpyAsync(ps->h_ctl, ps->d_ctl, kCtlInts * sizeof(int), hipMemcpyDeviceToHost, st));
     DPR_HIP(hipStreamSynchronize(st));
-    n = ps->h_count[0];
-    if ((size_t)n > ps->cap) return fail(DPR_ERR_DEVICE, "dpr_render_path: ray pool overflow (%d > %zu)", n, ps->cap);
+    total = PathStatsG{};
+    for (int i = 0; i < kStatLines; ++i) {
+      const PathStatsG* l = (const PathStatsG*)(ps->h_ctl + (kPathQueues + i) * kLineInts);
+      total.events += l->events;
+      total.shadow_steps += l->shadow_steps;
+      total.forwards += l->forwards;
+      total.stuck += l->stuck;
+      total.waves = std::max(total.waves, l->waves);
+    }
+    if (total.stuck) return fail(DPR_ERR_DEVICE, "dpr_render_path: more than %d waves", kMaxWaves);
+    n_in = ps->h_ctl[(kPathQueues + kStatLines) * kLineInts];
+    if (n_in == 0) break;
+    if ((size_t)n_in > ps->cap) return fail(DPR_ERR_DEVICE, "dpr_render_path: ray pool overflow (%d > %zu)", n_in, ps->cap);
+    in = ps->pool[cur];
+    cur ^= 1;
+    // the heads and the pool's size, not the statistics
+    hipLaunchKernelGGL(path_reset_kernel, dim3(1), dim3(256), 0, st, ps->d_ctl, kPathQueues * kLineInts);
+    hipLaunchKernelGGL(path_reset_kernel, dim3(1), dim3(64), 0, st,
+                       ps->d_ctl + (kPathQueues + kStatLines) * kLineInts, kLineInts);
   }
-  const int P = out->w * out->h;
-  hipLaunchKernelGGL(path_resolve_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, pg, P,
-                     (float4*)out->rgba, out->depth);
-  DPR_HIP(hipGetLastError());
-  unsigned long long hs[5] = {0, 0, 0, 0, 0};
-  DPR_HIP(hipMemcpyAsync(hs, ps->d_stats, sizeof(hs), hipMemcpyDeviceToHost, st));
-  DPR_HIP(hipStreamSynchronize(st));
-  if (hs[3]) return fail(DPR_ERR_DEVICE, "dpr_render_path: %llu rays did not fit the pool", hs[3]);
   if (stats) {
     stats->paths = n_paths;
-    stats->events = (int64_t)hs[0];
-    stats->shadow_steps = (int64_t)hs[1];
-    stats->forwards = (int64_t)hs[2];
-    stats->waves = (int32_t)hs[4];
+    stats->events = (int64_t)total.events;
+    stats->shadow_steps = (int64_t)total.shadow_steps;
+    stats->forwards = (int64_t)total.forwards;
+    stats->waves = (int32_t)total.waves;
   }
   return DPR_OK;
 }
