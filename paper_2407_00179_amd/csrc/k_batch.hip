@@ -1,7 +1,8 @@
 // Batched rendering of many cameras over uneven bricks.
 //
 // One persistent launch walks a queue of (camera, brick, screen tile) items.
-// Each wave pops a chunk of an item with one atomic, takes its rays as a pool, and
+// Each workgroup pops an item's 8 x 8 pixels with one atomic; each of its waves takes a
+// chunk of them at a time as a pool of rays and
 // marches them a few segments at a time, four lanes per ray; lanes whose ray has
 // finished (left the brick or terminated early) write its fragment and are refilled
 // from the pool with ballot/popcount compaction, so a wave is not held back by its
@@ -55,6 +56,12 @@ struct BatchG {
 
 // A march returns for a refill once fewer lanes than this are marching
 constexpr int kRefillLanes = 32;
+// Chunks that a workgroup takes from the queue at a time: one for each of its waves, so that
+// they march side by side and meet in the CU's L1 (a wave on its own: 37% more L1 misses on
+// the multi-camera batch of 27 FP16 bricks, 14.2 ms against 11.7).  Twice as many, or
+// workgroups of 8 or 16 waves, are slower (12.4 ms), and so are neighbouring tiles for the
+// waves of an XCD, which have half the L2 misses but crowd the same L2 channels (15.9 ms).
+constexpr int kShareChunks = 4;
 
 __global__ void zero_counts_kernel(int* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
@@ -63,15 +70,22 @@ __global__ void zero_counts_kernel(int* p, size_t n) {
 // A wave marches the queue's rays with the four lanes of a quad per ray (march.h), 16 at a
 // time: 4 x 4 pixel patches of a tile where the tile's shape allows.  What bounds it: the
 // chain of a launch's longest ray where a frame has few rays (one 256^3 brick at 1024^2:
-// 0.56 ms with one lane per ray, 0.14 ms with four), the texture path on bricks much larger
-// than the L2 (the 8 GB brick at 3840 x 2160: 12.5 -> 6.2 ms, a wave's loads meeting less than
-// half as many cache lines), VALU issue (94% busy) on the multi-camera batch of 27 FP16
-// bricks: 11.1 ms with one lane, 11.4 ms with four, which run everything.
+// 0.56 ms with one lane per ray, 0.14 ms with four), else the texture path, which is busy over
+// 80% of the time: a load of 64 scattered lanes takes 17 to 24 cycles whatever its width, and
+// L1 misses wait.  A fifth wave per SIMD pays where its registers do without spills (FP16
+// pairs: 94); more workgroups than have a share of the queue only cost their start.
 template <typename T, bool SKIP, bool WIDE, bool ISO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void batch_march_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 || ISO || WIDE ? 4 : 5))) void batch_march_kernel(
     SceneG sc, BatchG bg, const float4* __restrict__ tf) {
   extern __shared__ float4 tf_lds[];
   stage_tf_records(tf, sc.ntf, tf_lds, threadIdx.x, 256);
+  // the workgroup's share of the queue: chunks [next, end), taken under a lock
+  __shared__ int lock, share_next, share_end;
+  if (threadIdx.x == 0) {
+    lock = 0;
+    share_next = blockIdx.x * kShareChunks;
+    share_end = share_next + kShareChunks;
+  }
   __syncthreads();
 
   constexpr int L = 4;
@@ -80,13 +94,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
   const int tp = bg.tile_w * bg.tile_h;
   const bool patches = ((bg.tile_w | bg.tile_h) & 3) == 0;
   const int patches_x = bg.tile_w >> 2;
+  const bool squares = ((bg.tile_w | bg.tile_h) & 7) == 0;
+  const int squares_x = bg.tile_w >> 3;
 
-  // the queue's unit is a chunk of the rays of a wave (it divides every tile's pixels); a wave's first one is its own, so
-  // that a launch starts without thousands of atomics on one counter, and the first
-  // chunks go to different CUs
+  // the queue's unit is a chunk of the rays of a wave (it divides every tile's pixels)
   constexpr int kChunkRays = 64 / L;
   const int per_item = tp / kChunkRays, n_chunks = bg.n_items * per_item;
-  int first = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
 
   int cur_cam = -1, cur_brick = -1;
   int pool_item = -1, pool_next = 0, pool_left = 0;
@@ -103,11 +116,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
       if (idle == 0) break;
       if (pool_left == 0) {
         if (pending >= 0 || exhausted) break;
-        int c = first;
-        if (c < 0) {
-          if (lane == 0) c = atomicAdd(bg.head, 1) + 4 * gridDim.x;
+        int c = 0;
+        if (lane == 0) {
+          // (the holder's work is finite and needs no other wave, so every wait ends)
+          while (__hip_atomic_exchange(&lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
+          c = __hip_atomic_load(&share_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (c == __hip_atomic_load(&share_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) && c < n_chunks) {
+            c = (atomicAdd(bg.head, 1) + gridDim.x) * kShareChunks;
+            __hip_atomic_store(&share_end, c + kShareChunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+          // (past the queue's end nothing more is taken)
+          __hip_atomic_store(&share_next, c < n_chunks ? c + 1 : c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_store(&lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        first = -1;
         // wave-uniform: the item, and so the brick, live in scalar registers
         c = __builtin_amdgcn_readfirstlane(c);
         if (c >= n_chunks) {
@@ -137,7 +158,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
         const BatchItem I = ld_uniform(bg.items, pool_item);
         const CamG cam = ld_uniform(bg.cams, cur_cam);
         int ux, uy;  // pixel inside the tile
-        if (patches) {
+        if (squares) {
+          const int p = i >> 6, s = i >> 4;  // 8 x 8 pixels of four patches
+          ux = (p % squares_x) * 8 + (s & 1) * 4 + (i & 1) + ((i >> 1) & 2);
+          uy = (p / squares_x) * 8 + (s & 2) * 2 + ((i >> 1) & 1) + ((i >> 2) & 2);
+        } else if (patches) {
           const int p = i >> 4;
           ux = (p % patches_x) * 4 + (i & 3);
           uy = (p / patches_x) * 4 + ((i >> 2) & 3);
@@ -597,7 +622,10 @@ static hipError_t enqueue_batch(dpr_world w, BatchState* b, hipStream_t st, bool
   if (timed) (void)hipEventRecord(b->ev[0], st);
   const void* fn = march_fn(f16, b->skip, b->wide(), iso);
   void* args[] = {(void*)&sc, (void*)&g, (void*)&w->tf_dev};
-  const hipError_t le = hipLaunchKernel(fn, dim3(b->grid[iso]), dim3(256), args, lds, st);
+  // no more workgroups than have a share of the queue
+  const size_t shares = ((size_t)b->n_items * (b->tile_w * b->tile_h / 16) + kShareChunks - 1) / kShareChunks;
+  const unsigned grid = (unsigned)std::min<size_t>(b->grid[iso], std::max<size_t>(shares, 1));
+  const hipError_t le = hipLaunchKernel(fn, dim3(grid), dim3(256), args, lds, st);
   if (le != hipSuccess) return le;
   if (timed) (void)hipEventRecord(b->ev[1], st);
   const int tp = b->tile_w * b->tile_h;

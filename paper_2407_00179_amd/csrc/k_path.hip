@@ -281,11 +281,12 @@ struct ShadowQueue {
 //
 // A launch per wave with rays handed over through a pool in memory, and the host reading its
 // size every four, took 2170 us for 1024^2 paths of up to 4 bounces in 2 x 2 x 2 bricks of a
-// 512^3 volume (0.8 M tentative collisions in 12 launches of 38 to 277 us); one launch 290.
+// 512^3 volume (0.8 M tentative collisions in 12 launches of 38 to 277 us); one launch 366, 292 back to back.
 // It is bound by the latency of its longest chains (a flight's block majorants, then eight
 // voxels, per tentative collision), so a wave's paths come from all over the image: 16
-// pieces of 2 x 2 pixels per block (tiles of 8 x 8 pixels 515 us, four pieces of 4 x 4 335,
-// single pixels 302); bricks' descriptors in LDS gain 2%, a fourth wave per SIMD nothing.
+// pieces of 2 x 2 pixels per block (tiles of 8 x 8 pixels 440 us, four pieces of 4 x 4 335,
+// single pixels 302); bricks' descriptors in LDS gain 2%, a fourth wave per SIMD nothing
+// (all back to back).
 // With room for 256 shadow rays none is left over with up to 4 bounces (128: a second
 // launch, 663 us).
 template <typename T, bool WIDE>

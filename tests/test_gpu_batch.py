@@ -354,6 +354,8 @@ def test_autotune_cache(gpu_lib, dpr, tmp_path, monkeypatch):
 @pytest.mark.parametrize("nb, size, tile", [
     (1, (1040, 700), (8, 8)),     # a group of many sorted lists, one brick
     (7, (331, 260), (64, 1)),     # tiles that no 4 x 4 patch divides
+    (7, (250, 133), (12, 16)),    # tiles of 4 x 4 patches but not of 8 x 8 pixels
+    (2, (5, 3), (8, 8)),          # fewer shares of the queue than workgroups
     ((7, 5, 2), (150, 131), (16, 8)),    # more groups than the lanes of a wave, more than 16 on a tile
     ((8, 5, 5), (70, 66), (32, 32)),     # the largest tiles and composites
 ])
