@@ -94,16 +94,27 @@ struct Gather {
 // The loaded voxels of a sample's 8-voxel footprint, before decoding (FP16: the
 // four voxel pairs as loaded), so a request in flight holds as few registers as
 // possible.
-template <typename T>
-struct Voxels;
-template <>
-struct Voxels<float> {
+template <typename T, bool WIDE = false>
+struct Voxels {  // FP32, 32- and 64-bit offsets
   float v[8];
 };
 template <>
-struct Voxels<__half> {
+struct Voxels<__half, false> {
   uint32_t c[4];
 };
+// FP16 voxels without pairs: what lies from voxel x on and, where x ends a 4-voxel run, voxel
+// x + 1 from where the next run is.  They are put together only where the sample is used,
+// which is what waits for the loads: merged when requested, the march of an 8 GB brick at
+// 3840 x 2160 waited for each sample's voxels before it went on (9.7 ms with its commit; 8.7).
+template <>
+struct Voxels<__half, true> {
+  uint32_t c[4], next[4];
+  uint32_t sel;  // byte selector of the pair
+};
+__device__ __forceinline__ uint32_t voxel_pair(const Voxels<__half, false>& g, int k) { return g.c[k]; }
+__device__ __forceinline__ uint32_t voxel_pair(const Voxels<__half, true>& g, int k) {
+  return __builtin_amdgcn_perm(g.next[k], g.c[k], g.sel);
+}
 
 // Load the 8 voxels around base voxel (lx, ly, lz) (stored indices).  Byte offsets from
 // the brick base: 32-bit sums for bricks below 4 GiB; WIDE (the blocked array is 4 GiB
@@ -112,95 +123,114 @@ struct Voxels<__half> {
 // are global loads.  An FP16 brick is stored as voxel pairs when addressed with 32-bit
 // offsets and as 2-byte voxels when addressed with 64-bit offsets (the commit picks
 // the layout and the addressing together).
+//
+// In two parts.  Where an x-pair can straddle two 4-voxel runs, the lanes at a run's end read
+// their voxels lx + 1 on their own (load_run_ends), and only if a wave has such lanes.  A
+// wave waits for a sample by the number of loads issued after it, and the compiler has to
+// take the smallest possible: with a sample's second part between the next one's request and
+// its use, waiting for a sample meant waiting for most of the next one.  So a march asks
+// for the next sample's first part, waits for the present one (arrived), asks for the
+// next one's second part and goes on: eight partial frames of 256^3 FP32 bricks at 1024^2
+// 1.23 -> 0.99 ms, four frames of all of them 2.24 -> 2.04 ms.  (Requests two samples ahead
+// instead of one are slower: 1.12 and 2.14 ms.)
+struct Footed {
+  Foot f;
+  int lx;
+};
+template <typename T, bool WIDE>
+constexpr int kOffsetShift = WIDE ? 0 : 2;  // footprint's SH
+template <typename T, bool WIDE>
+__device__ __forceinline__ auto byte_offset(uint32_t e) {
+  if constexpr (WIDE)
+    return (uint64_t)e * sizeof(T);
+  else
+    return e;
+}
 template <typename T, bool WIDE, bool UNI>
-__device__ __forceinline__ void load_footprint(const BrickG& b, int lx, int ly, int lz, Voxels<T>& g) {
+__device__ __forceinline__ Footed load_footprint(const BrickG& b, int lx, int ly, int lz, Voxels<T, WIDE>& g) {
   using GC = const char __attribute__((address_space(1)))*;
-  if constexpr (sizeof(T) == 4) {
-    constexpr int SH = WIDE ? 0 : 2;
-    const Foot f = footprint<SH, UNI>(b, lx, ly, lz, in_block_x(lx));
-    // byte offset of the element at the sum of the per-axis terms
-    auto off = [](uint32_t e) {
-      if constexpr (WIDE)
-        return (uint64_t)e << 2;
-      else
-        return e;
-    };
-    const uint32_t a0 = f.a, a1 = f.a + f.dy, a2 = f.a + f.dz, a3 = a2 + f.dy;
-    // voxel lx + 1 follows voxel lx in memory unless lx ends a 4-voxel x-run, so
-    // each x-pair is one 8-byte load; lanes at a run's end read lx + 1 on their
-    // own.
-    const float2 c0 = load_pair_f32(b.data, off(a0)), c1 = load_pair_f32(b.data, off(a1));
-    const float2 c2 = load_pair_f32(b.data, off(a2)), c3 = load_pair_f32(b.data, off(a3));
-    g.v[0] = c0.x;
-    g.v[1] = c0.y;
-    g.v[2] = c1.x;
-    g.v[3] = c1.y;
-    g.v[4] = c2.x;
-    g.v[5] = c2.y;
-    g.v[6] = c3.x;
-    g.v[7] = c3.y;
-    if ((lx & 3) == 3) {
-      // from element 3 of a run to the block's second run, or to the next block
-      const uint32_t dx = (lx & 4) ? (512u - 67u) << SH : (64u - 3u) << SH;
-      g.v[1] = load_voxel_b<T>(b.data, off(a0 + dx));
-      g.v[3] = load_voxel_b<T>(b.data, off(a1 + dx));
-      g.v[5] = load_voxel_b<T>(b.data, off(a2 + dx));
-      g.v[7] = load_voxel_b<T>(b.data, off(a3 + dx));
+  const Foot f = footprint<kOffsetShift<T, WIDE>, UNI>(b, lx, ly, lz, in_block_x(lx));
+  const uint32_t a[4] = {f.a, f.a + f.dy, f.a + f.dz, f.a + f.dz + f.dy};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const auto o = byte_offset<T, WIDE>(a[k]);
+    if constexpr (sizeof(T) == 4) {
+      // voxel lx + 1 follows voxel lx in memory unless lx ends a 4-voxel x-run, so each
+      // x-pair is one 8-byte load
+      const float2 c = load_pair_f32(b.data, o);
+      g.v[2 * k] = c.x;
+      g.v[2 * k + 1] = c.y;
+    } else if constexpr (WIDE) {
+      // FP16 voxels (2 bytes: the layout of bricks addressed with 64-bit offsets): likewise
+      typedef uint32_t U2 __attribute__((aligned(2)));
+      g.c[k] = *(const U2 __attribute__((address_space(1)))*)((GC)b.data + o);
+    } else {
+      // FP16 voxel pairs (4 bytes, the layout of bricks below 4 GiB): each element
+      // holds the voxels (x, x + 1), one aligned 4-byte load per pair
+      g.c[k] = *(const uint32_t __attribute__((address_space(1)))*)((GC)b.data + o);
     }
-  } else if constexpr (WIDE) {
-    // FP16 voxels (2 bytes: the layout of bricks addressed with 64-bit offsets):
-    // the aligned 4-voxel run holding lx is one 8-byte load and the pair
-    // (lx, lx + 1) is shifted out of it; lanes whose lx ends a run read lx + 1 on
-    // their own.
-    using GU64 = const uint64_t __attribute__((address_space(1)))*;
-    using GU16 = const uint16_t __attribute__((address_space(1)))*;
-    const Foot f = footprint<0, UNI>(b, lx, ly, lz, ((uint32_t)lx & 4u) << 4);
-    auto off = [](uint32_t e) { return (uint64_t)e << 1; };
-    const uint32_t a0 = f.a, a1 = f.a + f.dy, a2 = f.a + f.dz, a3 = a2 + f.dy;
-    const uint32_t rs = (uint32_t)(lx & 3) << 4;
-    g.c[0] = (uint32_t)(*(GU64)((GC)b.data + off(a0)) >> rs);
-    g.c[1] = (uint32_t)(*(GU64)((GC)b.data + off(a1)) >> rs);
-    g.c[2] = (uint32_t)(*(GU64)((GC)b.data + off(a2)) >> rs);
-    g.c[3] = (uint32_t)(*(GU64)((GC)b.data + off(a3)) >> rs);
-    if ((lx & 3) == 3) {
-      // from the run's start to the block's second run, or to the next block
-      const uint32_t dx = (lx & 4) ? 512u - 64u : 64u;
-      g.c[0] = (g.c[0] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a0 + dx)) << 16);
-      g.c[1] = (g.c[1] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a1 + dx)) << 16);
-      g.c[2] = (g.c[2] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a2 + dx)) << 16);
-      g.c[3] = (g.c[3] & 0xffffu) | ((uint32_t) * (GU16)((GC)b.data + off(a3 + dx)) << 16);
-    }
-  } else {
-    // FP16 voxel pairs (4 bytes, the layout of bricks below 4 GiB): each element
-    // holds the voxels (x, x + 1), one aligned 4-byte load per pair
-    using GU = const uint32_t __attribute__((address_space(1)))*;
-    const Foot f = footprint<2, UNI>(b, lx, ly, lz, in_block_x(lx));
-    const uint32_t a2 = f.a + f.dz;
-    g.c[0] = *(GU)((GC)b.data + f.a);
-    g.c[1] = *(GU)((GC)b.data + (f.a + f.dy));
-    g.c[2] = *(GU)((GC)b.data + a2);
-    g.c[3] = *(GU)((GC)b.data + (a2 + f.dy));
   }
+  return {f, lx};
+}
+__device__ __forceinline__ void load_run_ends(const BrickG&, const Footed&, Voxels<__half, false>&) {}
+template <typename T, bool WIDE>
+__device__ __forceinline__ void load_run_ends(const BrickG& b, const Footed& p, Voxels<T, WIDE>& g) {
+  if constexpr (sizeof(T) == 2) {
+    g.sel = 0x03020100u;
+    // (not read unless lx ends a run)
+    asm("" : "=v"(g.next[0]), "=v"(g.next[1]), "=v"(g.next[2]), "=v"(g.next[3]));
+  }
+  if ((p.lx & 3) == 3) {
+    // from element 3 of a run to the block's second run, or to the next block
+    constexpr int SH = kOffsetShift<T, WIDE>;
+    const uint32_t e = p.f.a + ((p.lx & 4) ? (512u - 67u) << SH : (64u - 3u) << SH);
+    const uint32_t a[4] = {e, e + p.f.dy, e + p.f.dz, e + p.f.dz + p.f.dy};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const auto o = byte_offset<T, WIDE>(a[k]);
+      if constexpr (sizeof(T) == 4)
+        g.v[2 * k + 1] = load_voxel_b<T>(b.data, o);
+      else
+        g.next[k] = *(const uint16_t __attribute__((address_space(1)))*)(
+            (const char __attribute__((address_space(1)))*)b.data + o);
+    }
+    if constexpr (sizeof(T) == 2) g.sel = 0x05040100u;
+  }
+}
+// Waits for a sample's voxels.
+template <bool WIDE>
+__device__ __forceinline__ void arrived(Voxels<float, WIDE>& g) {
+  asm volatile("" : "+v"(g.v[0]), "+v"(g.v[1]), "+v"(g.v[2]), "+v"(g.v[3]), "+v"(g.v[4]), "+v"(g.v[5]), "+v"(g.v[6]),
+               "+v"(g.v[7]));
+}
+__device__ __forceinline__ void arrived(Voxels<__half, false>& g) {
+  asm volatile("" : "+v"(g.c[0]), "+v"(g.c[1]), "+v"(g.c[2]), "+v"(g.c[3]));
+}
+__device__ __forceinline__ void arrived(Voxels<__half, true>& g) {
+  asm volatile("" : "+v"(g.c[0]), "+v"(g.c[1]), "+v"(g.c[2]), "+v"(g.c[3]), "+v"(g.next[0]), "+v"(g.next[1]),
+               "+v"(g.next[2]), "+v"(g.next[3]));
 }
 
 // Load the 8 voxels around a sample point.
 template <typename T, bool WIDE>
-__device__ __forceinline__ void load_voxels(const SceneG& sc, const BrickG& b, const int64_t p[3], Voxels<T>& g) {
-  load_footprint<T, WIDE, false>(b, axis_index(p[0], sc.dims[0], b.slo[0], b.sdim[0]),
-                                 axis_index(p[1], sc.dims[1], b.slo[1], b.sdim[1]),
-                                 axis_index(p[2], sc.dims[2], b.slo[2], b.sdim[2]), g);
+__device__ __forceinline__ void load_voxels(const SceneG& sc, const BrickG& b, const int64_t p[3], Voxels<T, WIDE>& g) {
+  load_run_ends(b,
+                         load_footprint<T, WIDE, false>(b, axis_index(p[0], sc.dims[0], b.slo[0], b.sdim[0]),
+                                                        axis_index(p[1], sc.dims[1], b.slo[1], b.sdim[1]),
+                                                        axis_index(p[2], sc.dims[2], b.slo[2], b.sdim[2]), g),
+                         g);
 }
 
 // The 8 footprint voxels as FP32: (x0, x1) at (y0, z0), (y1, z0), (y0, z1), (y1, z1).
-template <typename T>
-__device__ __forceinline__ void decode_voxels(const Voxels<T>& g, float v[8]) {
+template <typename T, bool WIDE>
+__device__ __forceinline__ void decode_voxels(const Voxels<T, WIDE>& g, float v[8]) {
   if constexpr (sizeof(T) == 4) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = g.v[k];
   } else {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const float2 c = unpack_pair_f16(g.c[k]);
+      const float2 c = unpack_pair_f16(voxel_pair(g, k));
       v[2 * k] = c.x;
       v[2 * k + 1] = c.y;
     }
@@ -218,9 +248,9 @@ __device__ __forceinline__ void sample_frac(const SceneG& sc, const int64_t p[3]
 template <typename T, bool WIDE>
 __device__ __forceinline__ void gather(const SceneG& sc, const BrickG& b, const int64_t p[3], Gather<T>& g) {
   sample_frac(sc, p, g.fx, g.fy, g.fz);
-  Voxels<T> raw;
+  Voxels<T, WIDE> raw;
   load_voxels<T, WIDE>(sc, b, p, raw);
-  decode_voxels<T>(raw, g.v);
+  decode_voxels(raw, g.v);
 }
 
 template <typename T>
@@ -326,9 +356,9 @@ __device__ __forceinline__ int local_axis(int64_t p, int top, float& f) {
 }
 
 // A requested sample: its voxels and trilinear fractions.
-template <typename T>
+template <typename T, bool WIDE = false>
 struct Sample {
-  Voxels<T> v;
+  Voxels<T, WIDE> v;
   float fx, fy, fz;
 };
 
@@ -344,25 +374,33 @@ __device__ __forceinline__ float lerp_yz(float c00, float c01, float c10, float 
   const float c0 = fmaf(fy, c01 - c00, c00), c1 = fmaf(fy, c11 - c10, c10);
   return fmaf(fz, c1 - c0, c0);
 }
-__device__ __forceinline__ float sample_value(const Sample<float>& s) {
+template <bool WIDE>
+__device__ __forceinline__ float sample_value(const Sample<float, WIDE>& s) {
   const float* v = s.v.v;
   return lerp_yz(fmaf(s.fx, v[1] - v[0], v[0]), fmaf(s.fx, v[3] - v[2], v[2]), fmaf(s.fx, v[5] - v[4], v[4]),
                  fmaf(s.fx, v[7] - v[6], v[6]), s.fy, s.fz);
 }
-__device__ __forceinline__ float sample_value(const Sample<__half>& s) {
+template <bool WIDE>
+__device__ __forceinline__ float sample_value(const Sample<__half, WIDE>& s) {
   auto lerp_x = [&](uint32_t c) {
     return fmaf(s.fx, pair_diff(c), __half2float(__ushort_as_half((unsigned short)(c & 0xffffu))));
   };
-  return lerp_yz(lerp_x(s.v.c[0]), lerp_x(s.v.c[1]), lerp_x(s.v.c[2]), lerp_x(s.v.c[3]), s.fy, s.fz);
+  return lerp_yz(lerp_x(voxel_pair(s.v, 0)), lerp_x(voxel_pair(s.v, 1)), lerp_x(voxel_pair(s.v, 2)),
+                 lerp_x(voxel_pair(s.v, 3)), s.fy, s.fz);
 }
 
-// Request the 8 voxels around a point in stored voxel indices of a wave-uniform brick.
+// Request the 8 voxels around a point in stored voxel indices of a wave-uniform brick: the
+// first part; all.
 template <typename T, bool WIDE>
-__device__ __forceinline__ void request(const BrickG& b, int64_t x, int64_t y, int64_t z, Sample<T>& g) {
+__device__ __forceinline__ Footed request_first(const BrickG& b, int64_t x, int64_t y, int64_t z, Sample<T, WIDE>& g) {
   const int lx = local_axis(x, b.sdim[0] - 2, g.fx);
   const int ly = local_axis(y, b.sdim[1] - 2, g.fy);
   const int lz = local_axis(z, b.sdim[2] - 2, g.fz);
-  load_footprint<T, WIDE, true>(b, lx, ly, lz, g.v);
+  return load_footprint<T, WIDE, true>(b, lx, ly, lz, g.v);
+}
+template <typename T, bool WIDE>
+__device__ __forceinline__ void request(const BrickG& b, int64_t x, int64_t y, int64_t z, Sample<T, WIDE>& g) {
+  load_run_ends(b, request_first<T, WIDE>(b, x, y, z, g), g.v);
 }
 
 // Set up lane k's part of a ray: ray_begin, then the points of segments s0 + k,
@@ -394,7 +432,7 @@ __device__ __forceinline__ bool lane_begin(const SceneG& sc, const BrickG& b, co
     r.pv = 0.f;
     r.pst = 0;
     if ((double)f.s0 * sc.dt >= f.t_in) {
-      Sample<T> s;
+      Sample<T, WIDE> s;
       request<T, WIDE>(b, p[0] - f.dp[0], p[1] - f.dp[1], p[2] - f.dp[2], s);
       r.pv = sample_value(s);
       r.pst = kIsoPair | kIsoKnown | (r.pv >= sc.iso ? kIsoSide : 0);
@@ -414,7 +452,7 @@ __device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const
   const int64_t qp[3] = {q[0] - dq[0], q[1] - dq[1], q[2] - dq[2]};
   float vp = pv;
   if (!(pst & kIsoKnown)) {  // the previous sample was skipped: its value now
-    Sample<T> g;
+    Sample<T, WIDE> g;
     request<T, WIDE>(b, qp[0], qp[1], qp[2], g);
     vp = sample_value(g);
   }
@@ -422,10 +460,10 @@ __device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const
   int64_t qh[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) qh[a] = qp[a] + __double2ll_rn((double)f * (double)dq[a]);
-  Sample<T> g;
+  Sample<T, WIDE> g;
   request<T, WIDE>(b, qh[0], qh[1], qh[2], g);
   float v[8];
-  decode_voxels<T>(g.v, v);
+  decode_voxels(g.v, v);
   // d/dx, d/dy, d/dz of the patch: the edge differences, interpolated in the other two axes
   const float x0 = fmaf(g.fy, (v[3] - v[2]) - (v[1] - v[0]), v[1] - v[0]);
   const float x1 = fmaf(g.fy, (v[7] - v[6]) - (v[5] - v[4]), v[5] - v[4]);
@@ -481,7 +519,7 @@ __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, 
   int hit = -1;  // iso-surfaces: L * (step of the trip) + (lane of the ray) of the sample behind the surface
 
   // the next L samples, in order; i: step of the trip
-  auto step = [&](const Sample<T>& s, int i) {
+  auto step = [&](const Sample<T, WIDE>& s, int i) {
     const float v = sample_value(s);
     const float x = __builtin_amdgcn_fmed3f((v - sc.tf_lo) * sc.tf_scale, 0.f, x_max);
     const int j = min((int)x, sc.ntf - 2);
@@ -611,7 +649,7 @@ __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, 
     }
   };
 
-  Sample<T> g[NB];
+  Sample<T, WIDE> g[NB];
   bool pre = false;      // g[0 .. NB - 2] hold the samples at q, q + d, ...
   float mj_next = 0.f;
   bool have_mj = false;  // mj_next is the majorant at q
@@ -619,7 +657,12 @@ __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, 
   for (int trip = 0; !done && trip < max_trips; ++trip) {
     if (__popcll(__ballot(1)) < min_lanes) break;
     if constexpr (SKIP) {
-      const float mj = have_mj ? mj_next : majorant(q0, q1, q2);
+      float mj = mj_next;
+      if (!have_mj) {
+        mj = majorant(q0, q1, q2);
+        // (waits here, and not for the voxels requested ahead where the majorant was, too)
+        asm volatile("" : "+v"(mj));
+      }
       if (empty_at(mj)) {
         // the steps each lane makes inside its own macrocell.  A macrocell's range covers
         // half a voxel around the samples it holds, so the rounding of these distances
@@ -667,13 +710,16 @@ __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, 
           have_mj = true;
         }
       }
-      request<T, WIDE>(b, x, y, z, g[(i + NB - 1) % NB]);
+      Sample<T, WIDE>& ahead = g[(i + NB - 1) % NB];
+      const Footed foot = request_first<T, WIDE>(b, x, y, z, ahead);
       // (a chain of additions: left alone, the compiler keeps every multiple of d in registers)
       x += d0;
       y += d1;
       z += d2;
       asm("" : "+v"(x), "+v"(y), "+v"(z));
-      // (keeps the step's first uses of its voxels, which wait for them, behind the request)
+      __builtin_amdgcn_sched_barrier(0);
+      arrived(g[i % NB].v);
+      load_run_ends(b, foot, ahead.v);
       __builtin_amdgcn_sched_barrier(0);
       step(g[i % NB], i);
     }
