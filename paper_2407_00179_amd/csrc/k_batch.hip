@@ -214,8 +214,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       const int min_lanes = (!exhausted && pending < 0) ? kRefillLanes : 0;
       if (lane_advance<T, SKIP, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, cur_brick), tf_lds, r, LaneCfg<L>::kTrips,
                                               min_lanes)) {
+        const float4 rgba = ray_rgba<L>(r);
         if (k == L - 1) {
-          bg.frag_rgba[slot] = make_float4(r.cr, r.cg, r.cb, 1.f - r.tr);
+          bg.frag_rgba[slot] = rgba;
           bg.frag_depth[slot] = r.t_in;
           if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
         }

@@ -304,9 +304,10 @@ __global__ __launch_bounds__(256) void train_forward_blocked_kernel(
     if (r.m + k >= 0 && k == 0) w[c] = r.acc;
     if (lane_advance<float, false, false, false, 4, true>(sc, b, tf_lds, r, kCkpt / (4 * LaneCfg<4>::R), 0)) break;
   }
+  const float4 rgba = ray_rgba<4>(r);
   if (k == 3) {
     w[0] = r.acc;
-    out[ray] = make_float4(r.cr, r.cg, r.cb, 1.f - r.tr);
+    out[ray] = rgba;
     out_depth[ray] = r.t_in;
   }
 }
@@ -1035,7 +1036,8 @@ __global__ __launch_bounds__(256) void train_chunk_kernel(SceneG sc, BrickG b, c
   r.tr = __expf(-(float)r.acc);
   r.dl_cur = sc.density * sc.dt_f;
   lane_advance<float, false, false, false, 4, true>(sc, b, tf_lds, r, kCkpt / (4 * LaneCfg<4>::R), 0);
-  if (k == 0) col[ray * chunks + chunk] = make_float4(r.cr, r.cg, r.cb, 0.f);
+  const float4 rgba = ray_rgba<4>(r);
+  if (k == 0) col[ray * chunks + chunk] = rgba;
 }
 
 // clears the table sums and the tile queues behind them

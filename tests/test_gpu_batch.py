@@ -402,3 +402,31 @@ def test_moving_camera_queue(gpu_lib, dpr, nb, size, tile):
         f.release()
     w.release()
     dev.release()
+
+
+@pytest.mark.parametrize("dtype, flags", [(np.float32, 0), (np.float16, 0), (np.float16, 0x10)])  # (0x10: 2-byte voxels)
+@pytest.mark.parametrize("mc, step, ert", [(2, 1.0, 0.9), (2, 0.3, 1.0), (64, 0.45, 0.99)])
+def test_one_and_four_lanes_sum_alike(gpu_lib, dpr, dtype, flags, mc, step, ert):
+    """Four lanes per ray (batched) and one (plain) work in the same groups of four samples:
+    the same bits where macrocells hold fewer samples than a group, where rays end inside a
+    group, on an iso-surface, and with skipping off."""
+    assert dpr.FLAG_F16_HALVES == 0x10
+    dims, vol, boxes, tf = _scene(dtype)
+    tf[:60, 3] = 0.0   # (empty macrocells between the blobs)
+    prm = RenderParams(step, ert, 60.0)
+    cams = _cams(dims)
+    for skip in (0, dpr.FLAG_NO_SKIP):
+        w = make_world(dpr, gpu_lib, vol, dims, boxes, tf, prm, cams[0], mc=mc, flags=flags | skip)
+        frames = [dpr.Frame(gpu_lib, c.width, c.height) for c in cams]
+        for iso in (None, 0.45):
+            if iso is not None:
+                w.set_isosurface(iso, 0.25, 0.75)
+            w.render_batch(cams, frames, dpr.FLAG_PLAIN)
+            want = [frame_np(f)[:2] for f in frames]
+            w.render_batch(cams, frames)
+            for (a, z), f in zip(want, frames):
+                got = frame_np(f)[:2]
+                assert np.array_equal(got[0], a) and np.array_equal(got[1], z), (skip, iso)
+        for f in frames:
+            f.release()
+        w.release()
