@@ -1126,7 +1126,8 @@ static dpr_status scratch_end(dpr_device dev) {
 }
 
 // The blocked copies of a volume, where they can be had: below 4 GiB (32-bit offsets), when
-// the memory is there, and outside stream capture.  Else the kernels on the linear layout run.
+// the memory is there, and outside stream capture.  Else the kernels on the linear layout
+// run, and where they are the faster ones (train_small, train_coarse).
 struct TrainBlocks {
   float* vol = nullptr;
   float* grad = nullptr;
@@ -1160,6 +1161,40 @@ static bool train_blocks(dpr_device dev, const TrainG& g, bool grad, TrainBlocks
   if (!t.vol || (grad && !t.grad)) return false;
   t.n_runs = (uint32_t)(n / 4);
   return true;
+}
+
+// Where the kernels on the linear layout are the faster ones, by the work in ray-voxels (rays
+// times the longest extent).  Measured, a forward and backward on the blocked copies / with
+// the linear backward / with both linear:
+// - a launch so small that the copies' kernels cost more than they save:
+//    33^3,  1 camera  at  65^2 (0.14 M)  200 /  183 /  173 us
+//    40^3,  1 camera  at 100^2 (0.4 M)   188 /  182 /  173 us
+//    64^3,  4 cameras at  65^2 (1.1 M)   264 /  307 /  359 us
+// - the backward of many rays that lie voxels apart (at the volume's centre): they share no
+//   cells, and a patch around them is mostly empty, but few rays fill the chip only that way:
+//    64^3, 12 cameras at  65^2 (2.8 voxels, 3.2 M)   286 /  340 us
+//   200^3,  2 cameras at 100^2 (5.7 voxels, 4.0 M)   725 / 1214 us
+//   128^3,  4 cameras at 100^2 (3.6 voxels, 5.1 M)   985 /  669 us
+//   128^3, 12 cameras at  65^2 (5.6 voxels, 6.5 M)  1680 /  748 us
+//   200^3,  6 cameras at 200^2 (2.8 voxels, 48 M)   1434 / 1512 us
+//   128^3,  4 cameras at 181^2 (2.0 voxels, 17 M)    583 /  730 us
+constexpr double kSmallWork = 0.6e6, kCoarsePitch = 2.4, kCoarseWork = 4.5e6;
+static double train_work(const TrainG& g) {
+  return (double)g.n_cams * g.W * g.H * std::max(g.dims[0], std::max(g.dims[1], g.dims[2]));
+}
+static bool train_small(const TrainG& g) { return train_work(g) <= kSmallWork; }
+static bool train_coarse(const TrainG& g, const dpr_camera* cams) {
+  if (train_work(g) < kCoarseWork) return false;
+  double sum = 0.0;  // pixel pitches at the centre
+  for (int c = 0; c < g.n_cams; ++c) {
+    double d2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      const double d = cams[c].eye[a] - 0.5 * g.dims[a] * g.h;
+      d2 += d * d;
+    }
+    sum += std::sqrt(d2) * 2.0 * std::tan(cams[c].fovy_deg * M_PI / 360.0) / g.H;
+  }
+  return sum * g.inv_h >= kCoarsePitch * g.n_cams;
 }
 
 static SceneG train_scene(const TrainG& g) {
@@ -1266,7 +1301,7 @@ dpr_status dpr_render_train_forward(dpr_device dev, const float* volume, const i
   dim3 grid((unsigned)(tx * ty * n));
   size_t lds = 2 * sizeof(float4) * (size_t)n_tf;
   TrainBlocks t;
-  if (train_blocks(dev, g, false, t)) {
+  if (!train_small(g) && train_blocks(dev, g, false, t)) {
     if ((s = scratch_begin(dev)) != DPR_OK) return s;
     hipLaunchKernelGGL(block_volume_kernel, dim3(run_grid(t.n_runs, dev->cu_count)), dim3(256), 0, dev->stream, volume,
                        g.dims[0], g.dims[1], g.dims[2], t.nb[0], t.nb[1], t.n_runs, (float4*)t.vol, (float4*)nullptr);
@@ -1305,7 +1340,7 @@ dpr_status dpr_render_backward(dpr_device dev, const float* volume, const int64_
   int* heads = (int*)(dev->tf_grad64 + 4 * kMaxTF);
   if ((s = scratch_begin(dev)) != DPR_OK) return s;
   TrainBlocks t;
-  const bool blocked = train_blocks(dev, g, true, t);
+  const bool blocked = !train_small(g) && !train_coarse(g, cams) && train_blocks(dev, g, true, t);
   // Rays in pieces where whole ones would leave the chip's waves idle: up to kPieceTiles
   // tiles, while the intervals' colours take no more than kPieceBytes.
   TrainPieces pieces;

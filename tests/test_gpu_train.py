@@ -357,14 +357,16 @@ def test_cfg4_per_voxel_finite_differences(gpu_lib, dpr):
 
 
 @pytest.mark.parametrize("dims, n_cams, size, step, dist, n_tf, linear", [
-    ((33, 17, 26), 3, (65, 41), 0.5, None, 256, False),      # pieces of quarters, ragged tiles and blocks
+    ((33, 17, 26), 3, (95, 71), 0.5, None, 256, False),      # pieces of quarters, ragged tiles and blocks
     ((20, 18, 16), 300, (17, 9), 0.25, None, 2, False),      # pieces of tiles, smallest table
     ((10, 9, 8), 2100, (9, 9), 1.0, None, 1024, False),      # whole rays, largest table
-    ((120, 30, 40), 5, (20, 16), 1.0, None, 256, False),     # patches too wide for whole waves
-    ((24, 25, 31), 4, (30, 27), 0.3, 0.3, 64, False),        # cameras inside: rays of all axes in a wave
+    ((120, 30, 40), 20, (20, 16), 1.0, None, 256, False),    # patches too wide for whole waves
+    ((24, 25, 31), 30, (30, 27), 0.3, 0.3, 64, False),       # cameras inside: rays of all axes in a wave
     ((2, 3, 90), 4, (64, 64), 0.4, 0.2, 256, False),         # the thinnest volume
-    ((33, 17, 26), 3, (65, 41), 0.5, None, 256, True),       # no scratch: the linear layout
-    ((20, 18, 16), 3, (24, 20), 0.37, None, 1024, True),
+    ((33, 17, 26), 3, (65, 41), 0.5, None, 256, False),      # so little work that both ways are linear
+    ((120, 30, 40), 120, (18, 18), 0.5, None, 256, False),   # rays so far apart that the backward is linear
+    ((33, 17, 26), 3, (95, 71), 0.5, None, 256, True),       # no scratch: the linear layout
+    ((20, 18, 16), 30, (40, 28), 0.37, None, 1024, True),
 ])
 def test_gradients_over_launch_shapes(gpu_lib, dpr, monkeypatch, dims, n_cams, size, step, dist, n_tf, linear):
     """Every way the training kernels split their work, against the FP64 oracle."""
