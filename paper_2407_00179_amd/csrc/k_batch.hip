@@ -2,13 +2,8 @@
 //
 // One persistent launch walks a queue of (camera, brick, screen tile) items.
 // Each workgroup pops an item's 8 x 8 pixels with one atomic; each of its waves takes a
-// chunk of them at a time as a pool of rays and
-// marches them a few segments at a time, four lanes per ray; lanes whose ray has
-// finished (left the brick or terminated early) write its fragment and are refilled
-// from the pool with ballot/popcount compaction, so a wave is not held back by its
-// longest ray.  A
-// wave keeps one (camera, brick) at a time so brick and camera descriptors stay
-// wave-uniform.  A tile compositor then merges, per camera tile, the fragments of
+// chunk of them, 16 rays, at a time and marches them to their ends, four lanes per ray.
+// A tile compositor then merges, per camera tile, the fragments of
 // every item covering it.  The queue is built on the device (queue_kernel) from the
 // bricks' screen rectangles, so a frame of a moving camera costs the host a few
 // microseconds and no synchronization.  Repeated frames replay a HIP graph of march and
@@ -54,8 +49,6 @@ struct BatchG {
   int* slot_count;
 };
 
-// A march returns for a refill once fewer lanes than this are marching
-constexpr int kRefillLanes = 32;
 // Chunks that a workgroup takes from the queue at a time: one for each of its waves, so that
 // they march side by side and meet in the CU's L1 (a wave on its own: 37% more L1 misses on
 // the multi-camera batch of 27 FP16 bricks, 14.2 ms against 11.7).  Twice as many, or
@@ -72,10 +65,14 @@ __global__ void zero_counts_kernel(int* p, size_t n) {
 // chain of a launch's longest ray where a frame has few rays (one 256^3 brick at 1024^2:
 // 0.56 ms with one lane per ray, 0.14 ms with four), else the texture path, which is busy over
 // 80% of the time: a load of 64 scattered lanes takes 17 to 24 cycles whatever its width, and
-// L1 misses wait.  A fifth wave per SIMD pays where its registers do without spills (FP16
-// pairs: 94); more workgroups than have a share of the queue only cost their start.
+// L1 misses wait.  A wave's 16 rays end together as a rule: handing the lanes of those that
+// ended to others (once half had: 7.5 ms on two cameras at 2048^2 of 27 FP16 bricks; once an
+// eighth was left: 7.2; not at all: 7.0) costs more in ray set-up, in 64 bits and for few
+// lanes at a time, than it saves.  With 80 to 91 registers five or six waves run on a SIMD
+// (ISO: four); more by force only spills.  More workgroups than have a share of the queue
+// only cost their start.
 template <typename T, bool SKIP, bool WIDE, bool ISO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 || ISO || WIDE ? 4 : 5))) void batch_march_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void batch_march_kernel(
     SceneG sc, BatchG bg, const float4* __restrict__ tf) {
   extern __shared__ float4 tf_lds[];
   stage_tf_records(tf, sc.ntf, tf_lds, threadIdx.x, 256);
@@ -90,7 +87,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 
   constexpr int L = 4;
   const int lane = threadIdx.x & 63, k = lane & (L - 1);
-  const uint64_t lt_mask = ~(~0ull << (lane & (64 - L)));  // the lanes of lower rays
   const int tp = bg.tile_w * bg.tile_h;
   const bool patches = ((bg.tile_w | bg.tile_h) & 3) == 0;
   const int patches_x = bg.tile_w >> 2;
@@ -101,127 +97,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   constexpr int kChunkRays = 64 / L;
   const int per_item = tp / kChunkRays, n_chunks = bg.n_items * per_item;
 
-  int cur_cam = -1, cur_brick = -1;
-  int pool_item = -1, pool_next = 0, pool_left = 0;
-  int pending = -1;  // a chunk
-  bool exhausted = false;
-  bool active = false;
-  LaneRay r;
-  size_t slot = 0;
-
-  while (true) {
-    // ---- refill idle lanes from the current item's pool
-    while (true) {
-      const uint64_t idle = __ballot(!active);
-      if (idle == 0) break;
-      if (pool_left == 0) {
-        if (pending >= 0 || exhausted) break;
-        int c = 0;
-        if (lane == 0) {
-          // (the holder's work is finite and needs no other wave, so every wait ends)
-          while (__hip_atomic_exchange(&lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
-          c = __hip_atomic_load(&share_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (c == __hip_atomic_load(&share_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) && c < n_chunks) {
-            c = (atomicAdd(bg.head, 1) + gridDim.x) * kShareChunks;
-            __hip_atomic_store(&share_end, c + kShareChunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          }
-          // (past the queue's end nothing more is taken)
-          __hip_atomic_store(&share_next, c < n_chunks ? c + 1 : c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          __hip_atomic_store(&lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        // wave-uniform: the item, and so the brick, live in scalar registers
-        c = __builtin_amdgcn_readfirstlane(c);
-        if (c >= n_chunks) {
-          exhausted = true;
-          break;
-        }
-        const int it = c / per_item;
-        if (bg.item_count && lane == 0 && c % per_item == 0) atomicAdd(bg.item_count + it, 1);
-        const BatchItem I = ld_uniform(bg.items, it);
-        if (I.cam != cur_cam || I.brick != cur_brick) {
-          if (__ballot(active) != 0) {  // drain the current rays first
-            pending = c;
-            break;
-          }
-          cur_cam = I.cam;
-          cur_brick = I.brick;
-        }
-        pool_item = it;
-        pool_next = (c % per_item) * kChunkRays;
-        pool_left = kChunkRays;
+  for (;;) {
+    int c = 0;
+    if (lane == 0) {
+      // (the holder's work is finite and needs no other wave, so every wait ends)
+      while (__hip_atomic_exchange(&lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) __builtin_amdgcn_s_sleep(1);
+      c = __hip_atomic_load(&share_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (c == __hip_atomic_load(&share_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) && c < n_chunks) {
+        c = (atomicAdd(bg.head, 1) + gridDim.x) * kShareChunks;
+        __hip_atomic_store(&share_end, c + kShareChunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
-      const int n_idle = __popcll(idle) / L;
-      const int take = min(n_idle, pool_left);
-      const int rank = __popcll(idle & lt_mask) / L;
-      if (!active && rank < take) {
-        const int i = pool_next + rank;
-        const BatchItem I = ld_uniform(bg.items, pool_item);
-        const CamG cam = ld_uniform(bg.cams, cur_cam);
-        int ux, uy;  // pixel inside the tile
-        if (squares) {
-          const int p = i >> 6, s = i >> 4;  // 8 x 8 pixels of four patches
-          ux = (p % squares_x) * 8 + (s & 1) * 4 + (i & 1) + ((i >> 1) & 2);
-          uy = (p / squares_x) * 8 + (s & 2) * 2 + ((i >> 1) & 1) + ((i >> 2) & 2);
-        } else if (patches) {
-          const int p = i >> 4;
-          ux = (p % patches_x) * 4 + (i & 3);
-          uy = (p / patches_x) * 4 + ((i >> 2) & 3);
-        } else {
-          ux = i % bg.tile_w;
-          uy = i / bg.tile_w;
-        }
-        const int px = I.tx * bg.tile_w + ux;
-        const int py = I.ty * bg.tile_h + uy;
-        slot = (size_t)I.slot * tp + uy * bg.tile_w + ux;
-        bool hit = false;
-        if (px < cam.W && py < cam.H) {
-          double d[3];
-          camera_ray(cam, px, py, d);
-          hit = lane_begin<T, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, cur_brick), cam.eye, d, k, r);
-        }
-        // (a hit with no samples is an empty fragment at its depth)
-        const bool none = hit && r.m + k < 0;
-        if (hit && !none) {
-          active = true;
-        } else if (k == 0) {
-          bg.frag_rgba[slot] = make_float4(0.f, 0.f, 0.f, 0.f);
-          bg.frag_depth[slot] = none ? r.t_in : INFINITY;
-          if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
-        }
-      }
-      pool_next += take;
-      pool_left -= take;
+      // (past the queue's end nothing more is taken)
+      __hip_atomic_store(&share_next, c < n_chunks ? c + 1 : c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_store(&lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    // ---- nothing to march: switch to the pending item or finish
-    if (__ballot(active) == 0) {
-      if (pending >= 0) {
-        pool_item = pending / per_item;
-        pool_next = (pending % per_item) * kChunkRays;
-        pool_left = kChunkRays;
-        const BatchItem I = ld_uniform(bg.items, pool_item);
-        cur_cam = I.cam;
-        cur_brick = I.brick;
-        pending = -1;
-        continue;
-      }
-      if (exhausted) break;
-      continue;
+    // wave-uniform: the item, and so the camera and the brick, live in scalar registers
+    c = __builtin_amdgcn_readfirstlane(c);
+    if (c >= n_chunks) break;
+    const int it = c / per_item, first = (c % per_item) * kChunkRays;
+    if (bg.item_count && lane == 0 && first == 0) atomicAdd(bg.item_count + it, 1);
+    const BatchItem I = ld_uniform(bg.items, it);
+    const int i = first + lane / L;
+    int ux, uy;  // pixel inside the tile
+    if (squares) {
+      const int p = i >> 6, s = i >> 4;  // 8 x 8 pixels of four patches
+      ux = (p % squares_x) * 8 + (s & 1) * 4 + (i & 1) + ((i >> 1) & 2);
+      uy = (p / squares_x) * 8 + (s & 2) * 2 + ((i >> 1) & 1) + ((i >> 2) & 2);
+    } else if (patches) {
+      const int p = i >> 4;
+      ux = (p % patches_x) * 4 + (i & 3);
+      uy = (p / patches_x) * 4 + ((i >> 2) & 3);
+    } else {
+      ux = i % bg.tile_w;
+      uy = i / bg.tile_w;
     }
-    // ---- march a chunk of segments
-    if (active) {
-      // early return for a refill (fewer than half the lanes marching), only while
-      // a refill can take rays
-      const int min_lanes = (!exhausted && pending < 0) ? kRefillLanes : 0;
-      if (lane_advance<T, SKIP, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, cur_brick), tf_lds, r, LaneCfg<L>::kTrips,
-                                              min_lanes)) {
-        const float4 rgba = ray_rgba<L>(r);
-        if (k == L - 1) {
-          bg.frag_rgba[slot] = rgba;
-          bg.frag_depth[slot] = r.t_in;
-          if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
-        }
-        active = false;
+    const int px = I.tx * bg.tile_w + ux, py = I.ty * bg.tile_h + uy;
+    const CamG cam = ld_uniform(bg.cams, I.cam);
+    float4 rgba = make_float4(0.f, 0.f, 0.f, 0.f);
+    float z = INFINITY;
+    if (px < cam.W && py < cam.H) {
+      double d[3];
+      camera_ray(cam, px, py, d);
+      LaneRay r;
+      if (lane_begin<T, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, I.brick), cam.eye, d, k, r)) {
+        lane_advance<T, SKIP, WIDE, ISO, L>(sc, ld_uniform(bg.bricks, I.brick), tf_lds, r, 0x7fffffff);
+        rgba = ray_rgba<L>(r);
+        z = r.t_in;
       }
+    }
+    if (k == L - 1) {
+      const size_t slot = (size_t)I.slot * tp + uy * bg.tile_w + ux;
+      bg.frag_rgba[slot] = rgba;
+      bg.frag_depth[slot] = z;
+      if (bg.slot_count) atomicAdd(bg.slot_count + slot, 1);
     }
   }
 }

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void march_kernel(SceneG sc, BrickG b, CamG ca
   LaneRay r;
   const size_t p = (size_t)py * cam.W + px;
   if (lane_begin<T, WIDE, ISO, 1>(sc, b, cam.eye, d, 0, r)) {
-    lane_advance<T, SKIP, WIDE, ISO, 1>(sc, b, tf_lds, r, 0x7fffffff, 0);
+    lane_advance<T, SKIP, WIDE, ISO, 1>(sc, b, tf_lds, r, 0x7fffffff);
     out_rgba[p] = ray_rgba<1>(r);
     out_depth[p] = r.t_in;
   } else {

@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) void train_forward_blocked_kernel(
   double* w = ws + ray * ws_stride;
   for (int c = 1;; ++c) {
     if (r.m + k >= 0 && k == 0) w[c] = r.acc;
-    if (lane_advance<float, false, false, false, 4, true>(sc, b, tf_lds, r, kCkpt / (4 * LaneCfg<4>::R), 0)) break;
+    if (lane_advance<float, false, false, false, 4, true>(sc, b, tf_lds, r, kCkpt / (4 * LaneCfg<4>::R))) break;
   }
   const float4 rgba = ray_rgba<4>(r);
   if (k == 3) {
@@ -1038,7 +1038,7 @@ __global__ __launch_bounds__(256) void train_chunk_kernel(SceneG sc, BrickG b, c
   r.acc = ws[ray * ws_stride + 1 + chunk];
   r.tr = __expf(-(float)r.acc);
   r.dl_cur = sc.density * sc.dt_f;
-  lane_advance<float, false, false, false, 4, true>(sc, b, tf_lds, r, kCkpt / (4 * LaneCfg<4>::R), 0);
+  lane_advance<float, false, false, false, 4, true>(sc, b, tf_lds, r, kCkpt / (4 * LaneCfg<4>::R));
   const float4 rgba = ray_rgba<4>(r);
   if (k == 0) col[ray * chunks + chunk] = rgba;
 }

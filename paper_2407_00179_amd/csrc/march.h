@@ -292,7 +292,6 @@ constexpr int kRayDone = -(1 << 29);  // LaneRay::m of a ray that ended early
 template <int L>
 struct LaneCfg {
   static constexpr int NB = 2, R = L == 4 ? 2 : 4;
-  static constexpr int kTrips = 128 / (R * L);  // between refill checks: at most 128 samples of a ray
 };
 
 struct LaneRay {
@@ -512,11 +511,10 @@ __device__ __forceinline__ void iso_hit(const SceneG& sc, const BrickG& b, const
 
 // RAW: the table's values are not known to be finite (a sample of no optical depth adds
 // nothing, whatever its colour).
-// March until the ray ends (true), max_trips trips have passed, or fewer than
-// min_lanes lanes of the wave are still marching.  b is wave-uniform.
+// March until the ray ends (true) or max_trips trips have passed.  b is wave-uniform.
 template <typename T, bool SKIP, bool WIDE, bool ISO, int L, bool RAW = false>
 __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, const float4* tfr, LaneRay& r,
-                                             int max_trips, int min_lanes) {
+                                             int max_trips) {
   static_assert(L == 1 || L == 4, "one lane, or a DPP quad");
   constexpr int NB = LaneCfg<L>::NB, R = LaneCfg<L>::R;
   static_assert(R % NB == 0 && NB >= 2, "a trip ends with the buffers as it found them");
@@ -690,7 +688,6 @@ __device__ __forceinline__ bool lane_advance(const SceneG& sc, const BrickG& b, 
   bool have_mj = false;  // mj_next is the majorant at q
   bool done = m + k < 0;
   for (int trip = 0; !done && trip < max_trips; ++trip) {
-    if (__popcll(__ballot(1)) < min_lanes) break;
     if constexpr (SKIP) {
       float mj = mj_next;
       if (!have_mj) {
