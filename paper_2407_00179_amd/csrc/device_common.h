@@ -159,14 +159,16 @@ __device__ __forceinline__ T ld_global(const T* p, size_t i) {
   return ((const T __attribute__((address_space(1)))*)p)[i];
 }
 
-// Ray through pixel (px, py); returns the unit direction.
+// Ray through pixel (px, py); returns the unit direction.  The sums are spelled out: left to
+// contraction, the kernels take the squares in different orders, and a ray along an edge
+// that bricks share then hits a brick in one kernel and misses it in another.
 __device__ __forceinline__ void camera_ray(const CamG& c, int px, int py, double d[3]) {
   double x = (2.0 * (px + 0.5) / c.W - 1.0) * c.sx;
   double y = (1.0 - 2.0 * (py + 0.5) / c.H) * c.sy;
-  double v0 = c.f[0] + x * c.r[0] + y * c.u[0];
-  double v1 = c.f[1] + x * c.r[1] + y * c.u[1];
-  double v2 = c.f[2] + x * c.r[2] + y * c.u[2];
-  double inv = 1.0 / sqrt(v0 * v0 + v1 * v1 + v2 * v2);
+  double v0 = fma(y, c.u[0], fma(x, c.r[0], c.f[0]));
+  double v1 = fma(y, c.u[1], fma(x, c.r[1], c.f[1]));
+  double v2 = fma(y, c.u[2], fma(x, c.r[2], c.f[2]));
+  double inv = 1.0 / sqrt(fma(v2, v2, fma(v0, v0, v1 * v1)));
   d[0] = v0 * inv;
   d[1] = v1 * inv;
   d[2] = v2 * inv;

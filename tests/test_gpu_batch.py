@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from oracle import RenderParams
-from synth import Camera, even_split, fibonacci_cameras, kd_split, make_blobs, make_tf, make_volume_small
+from synth import Camera, even_split, fibonacci_cameras, kd_split, make_blobs, make_tf, make_volume_small, orbit_camera
 from tests.gpu_util import TOL_F32, frame_np, log, make_world, oracle_brick
 
 pytestmark = pytest.mark.gpu
@@ -430,3 +430,34 @@ def test_one_and_four_lanes_sum_alike(gpu_lib, dpr, dtype, flags, mc, step, ert)
         for f in frames:
             f.release()
         w.release()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_rays_along_a_shared_edge(gpu_lib, dpr, dtype):
+    """Rays in the plane of the edge that four bricks share have chords of length zero or of
+    a rounding in two of them: the batched and the plain launch agree on every one of them."""
+    dims = (378, 258, 24)
+    vol = make_volume_small(dims, make_blobs(dims, 5, 4, (0.1, 0.3)), 6, 0.02, dtype)
+    boxes = even_split(dims, (2, 2, 1))
+    cams = [orbit_camera(dims, 43, 565, az_deg=10.0 + 31.0 * i, el_deg=10.0 + 2.0 * i) for i in range(11)]
+    w = make_world(dpr, gpu_lib, vol, dims, boxes, make_tf(2001), RenderParams(0.5, 0.99, 60.0), cams[0], mc=16)
+    frames = [dpr.Frame(gpu_lib, c.width, c.height) for c in cams]
+    parts = [dpr.Frame(gpu_lib, cams[0].width, cams[0].height) for _ in range(2)]
+    w.render_batch(cams, frames, dpr.FLAG_PLAIN)
+    want = [frame_np(f)[:2] for f in frames]
+    w.render_batch(cams, frames)
+    for (a, z), f in zip(want, frames):
+        got = frame_np(f)[:2]
+        assert np.array_equal(got[0], a) and np.array_equal(got[1], z)
+    prm = (0.5, 0.99, 16)
+    for c in cams:
+        w.set_camera(c)
+        for i in range(len(boxes)):
+            for flags, f in zip((0, dpr.FLAG_PLAIN), parts):
+                w.set_params(dpr.Params(*prm, flags))
+                w.render_partial(i, f)
+            one, two = (frame_np(f)[:2] for f in parts)
+            assert np.array_equal(one[1], two[1]) and np.array_equal(one[0], two[0]), (c.eye, i)
+    for f in frames + parts:
+        f.release()
+    w.release()
